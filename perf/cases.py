@@ -427,6 +427,19 @@ def _adj(x):
     return x.conj().transpose(-1, -2)
 
 
+def _solve(A, B):
+    """A^{-1} B for batches whose A has a positive definite Hermitian part, by
+    2 x 2 blocks down to sizes that the batched LU takes."""
+    n = A.shape[-1]
+    if n <= 128:
+        return torch.linalg.solve(A, B)
+    h = n // 2
+    Y = _solve(A[..., :h, :h], torch.cat([A[..., :h, h:], B[..., :h, :]], -1))
+    E, F = Y[..., :n - h], Y[..., n - h:]
+    low = _solve(A[..., h:, h:] - _mm(A[..., h:, :h], E), B[..., h:, :] - _mm(A[..., h:, :h], F))
+    return torch.cat([F - _mm(E, low), low], -2)
+
+
 def _mm(a, b):
     return torch.matmul(a.resolve_conj().contiguous(), b.resolve_conj().contiguous())
 
@@ -482,7 +495,7 @@ class _Exact:
     def solve(self, P0t):
         """P~(i Omega) and P~(tau) of P0(tau)."""
         P0 = _apply(self.g["TB"], P0t)
-        Pw = torch.linalg.solve(torch.eye(self.n, dtype=C128, device=P0.device) - P0, P0)
+        Pw = _solve(torch.eye(self.n, dtype=C128, device=P0.device) - P0, P0)
         return Pw, _apply(self.g["TBp"], Pw)
 
     def sigma(self, G):
@@ -550,7 +563,7 @@ def exact(case, seed):
         if kind == "screened":
             P0 = _p_bare(c, seed, _grids(c)["nuB"])
             one = torch.eye(c["naux"], dtype=C128, device=dev)
-            return {"P_iw": torch.stack([torch.linalg.solve(one - p, p) for p in P0])}
+            return {"P_iw": torch.stack([_solve(one - p, p) for p in P0])}
         if kind == "mu":
             g = _grids(c)
             sinf, siw = _self_energy_poles(c, seed, g["nuF"])
