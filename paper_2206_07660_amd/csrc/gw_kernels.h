@@ -164,9 +164,12 @@ hipError_t dot_launch(long long n, const double2* X, const double2* Y, double* p
 // part[n*nk+k] = Re(r_n tr[P[n][k] S[k]]) (S per k: s_per_w = 0) or with S[n][k] (s_per_w = 1).
 hipError_t wtrace_launch(const double2* P, const double2* S, const double2* r, int nao, int nk, int nw,
                          double* part, hipStream_t st, int s_per_w = 0);
-// P[b] for b < nmat (n x n, row-major): entries below the diagonal become the
-// conjugates of their mirror images above it.
-hipError_t herm_fill_launch(double2* P, int n, long long nmat, hipStream_t st);
+// For b < nmat matrices (n x n, row-major) at src + b n^2: with herm, entries
+// below the diagonal become the conjugates of their mirror images above it
+// (only the upper triangle is read); with dst, dst + b dstep receives the
+// transpose of the (completed) matrix.
+hipError_t mirror_launch(double2* src, double2* dst, long long dstep, int n, long long nmat, bool herm,
+                         hipStream_t st);
 // P[b] <- (P[b] + P[b]^H) / 2 for b < nmat (n x n, row-major).
 hipError_t herm_avg_launch(double2* P, int n, long long nmat, hipStream_t st);
 // Eq. tilde_Phi_GW: for each of nmat matrices m of an LU-factorised I - P0

@@ -9,7 +9,7 @@
 //                (Eq. tilde_P_omega); its trailing updates are zgemm_k calls.
 //  * dyson_k     G = [(i w + mu) S - H0 - Sigma]^{-1} by Gauss-Jordan (Eq. Dyson),
 //                with the electron-count partials of gamma = -G(beta^-).
-//  * herm_fill_k, herm_avg_k   Hermitian fill / Hermitian part of matrices.
+//  * mirror_k, herm_avg_k   Hermitian fill and transposes / Hermitian part of matrices.
 //  * small reductions and vector kernels (sums, traces, mixing, axpby, dot).
 #include <hip/hip_runtime.h>
 
@@ -1427,18 +1427,72 @@ hipError_t bsgemm_launch(const SplitDesc& d, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
-// Lower triangle from the upper one: P[b](r, c) = conj(P[b](c, r)) for r > c.
-// Grid: x over the n*n entries of a matrix, y over the matrices; threads on
-// or above the diagonal do nothing.
-__global__ void herm_fill_k(double2* P, int n) {
-  const unsigned nn = (unsigned)n * (unsigned)n;
-  const unsigned e = blockIdx.x * 256u + threadIdx.x;
-  if (e >= nn) return;
-  const unsigned r = e / (unsigned)n, c = e - r * (unsigned)n;
-  if (r <= c) return;
-  double2* M = P + (size_t)blockIdx.y * nn;
-  const double2 v = M[(size_t)c * n + r];
-  M[e] = double2{v.x, -v.y};
+// Completes polarization matrices: one workgroup per 32 x 32 tile (with HERM
+// per tile on or above the diagonal) and matrix.  The tile goes through LDS,
+// so that both the tile and its transpose are read and written along rows
+// (bound by HBM: each entry read once, written once or twice).
+//   HERM: src(c, r) = conj(src(r, c)) for r < c;  dst = src^T
+//   else: dst = src^T
+constexpr int kMir = 32;
+
+template <bool HERM>
+__global__ void __launch_bounds__(256) mirror_k(double2* src, double2* dst, long long dstep, int n, int tiles) {
+  __shared__ double2 t[kMir][kMir + 1];
+  int tr = 0, tc = 0;
+  if constexpr (HERM) {
+    int e = blockIdx.x, len = tiles;
+    while (e >= len) {
+      e -= len;
+      ++tr;
+      --len;
+    }
+    tc = tr + e;
+  } else {
+    tr = blockIdx.x / tiles;
+    tc = blockIdx.x - tr * tiles;
+  }
+  double2* S = src + (size_t)blockIdx.y * n * n;
+  double2* D = dst ? dst + (long long)blockIdx.y * dstep : nullptr;
+  const int x = threadIdx.x & 31, y0 = threadIdx.x >> 5;
+  const int r0 = tr * kMir, c0 = tc * kMir;
+#pragma unroll
+  for (int y = y0; y < kMir; y += 8)
+    if (r0 + y < n && c0 + x < n) t[y][x] = S[(size_t)(r0 + y) * n + c0 + x];
+  __syncthreads();
+#pragma unroll
+  for (int y = y0; y < kMir; y += 8) {
+    // (r, c) of the transposed tile: row c0 + y, column r0 + x
+    const int r = c0 + y, c = r0 + x;
+    if (r < n && c < n) {
+      const double2 v = t[x][y];
+      if constexpr (HERM) {
+        if (r > c) S[(size_t)r * n + c] = double2{v.x, -v.y};
+        if (D && r >= c) D[(size_t)r * n + c] = v;
+      } else {
+        D[(size_t)r * n + c] = v;
+      }
+    }
+    if constexpr (HERM) {
+      const int ru = r0 + y, cu = c0 + x;
+      if (D && ru < cu && cu < n) {
+        const double2 v = t[y][x];
+        D[(size_t)ru * n + cu] = double2{v.x, -v.y};
+      }
+    }
+  }
+}
+
+hipError_t mirror_launch(double2* src, double2* dst, long long dstep, int n, long long nmat, bool herm,
+                         hipStream_t st) {
+  if (n <= 0 || nmat <= 0 || (!herm && !dst)) return hipSuccess;
+  const long long tiles = (n + kMir - 1) / kMir;
+  if (nmat > 65535) return hipErrorInvalidConfiguration;
+  const dim3 grid((unsigned)(herm ? tiles * (tiles + 1) / 2 : tiles * tiles), (unsigned)nmat, 1);
+  if (herm)
+    mirror_k<true><<<grid, 256, 0, st>>>(src, dst, dstep, n, (int)tiles);
+  else
+    mirror_k<false><<<grid, 256, 0, st>>>(src, dst, dstep, n, (int)tiles);
+  return hipGetLastError();
 }
 
 // Hermitian part: one thread per entry (r, c) with r <= c of each matrix; it
@@ -1535,14 +1589,6 @@ hipError_t phi_terms_launch(const double2* LU, const double2* P0, int n, long lo
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return sum_launch(part, nmat, 1.0, out, st);
-}
-
-hipError_t herm_fill_launch(double2* P, int n, long long nmat, hipStream_t st) {
-  if (n <= 0 || nmat <= 0) return hipSuccess;
-  if (nmat > 65535 || (long long)n * n > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-  const unsigned bx = (unsigned)(((long long)n * n + 255) / 256);
-  herm_fill_k<<<dim3(bx, (unsigned)nmat, 1), 256, 0, st>>>(P, n);
-  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
