@@ -48,6 +48,7 @@ struct gw_ctx {
   int split_cfg = -1;      // tile configuration of the split-bf16 contractions
   int split_group = 0;     // > 0: grouped workgroup order of the split contractions
   int herm = 0;            // gw_set_hermitian: GW_HERM_* bits
+  bool sym_b = false;      // bosonic tables symmetric under Omega -> -Omega and tau -> beta - tau
   double mu_window = 0.0;  // gw_set_mu_window: electron-count window (0: exact root)
   // measurement: event pairs per kernel class while profiling is on
   bool prof = false;
@@ -476,6 +477,30 @@ gw_status gw_grids_host(double beta, int ntau, const long long* nF, const long l
   return GW_OK;
 }
 
+// Whether the bosonic tables keep the symmetries of the exact transforms,
+// T(-Omega, tau) = conj T(Omega, tau) = T(Omega, beta - tau) and the same for
+// the fit.  Chebyshev tables do to 3e-12 of their largest entry (200 nodes);
+// IR tables of a small cutoff do not (1e-6 at lambda 500, eps 1e-12: their
+// last basis functions are rounding), nor need caller tables.
+static bool bosonic_symmetry(const gw_ctx* c) {
+  const int nt = c->d.ntau, nw = c->d.nw_b;
+  const double tol = 1e-11;
+  for (int n = 0; n < nw; ++n)
+    if (c->nB[n] != -c->nB[nw - 1 - n]) return false;
+  double mT = 0.0, mP = 0.0, dT = 0.0, dP = 0.0;
+  for (int n = 0; n < nw; ++n)
+    for (int i = 0; i < nt; ++i) {
+      const gwgrid::cd t = c->TB[(size_t)n * nt + i], q = c->TBp[(size_t)i * nw + n];
+      mT = std::max(mT, std::abs(t));
+      mP = std::max(mP, std::abs(q));
+      dT = std::max({dT, std::abs(c->TB[(size_t)(nw - 1 - n) * nt + i] - std::conj(t)),
+                     std::abs(c->TB[(size_t)n * nt + nt - 1 - i] - std::conj(t))});
+      dP = std::max({dP, std::abs(c->TBp[(size_t)i * nw + nw - 1 - n] - std::conj(q)),
+                     std::abs(c->TBp[(size_t)(nt - 1 - i) * nw + n] - std::conj(q))});
+    }
+  return dT <= tol * mT && dP <= tol * mP;
+}
+
 // Keep the host tables in the context and upload the device copies.
 static gw_status install_grids(gw_ctx* c, HostGrids& g) {
   c->tau = g.tau; c->x = g.x; c->w = g.w; c->nF = g.nF; c->nB = g.nB;
@@ -487,6 +512,7 @@ static gw_status install_grids(gw_ctx* c, HostGrids& g) {
   c->dTF = c->dTFp = c->dTB = c->dTBp = c->dw = c->drrow = nullptr;
   c->dwF = nullptr;
   c->grids = false;
+  c->sym_b = bosonic_symmetry(c);
   gw_status s;
   if ((s = upload(c, &c->dTF, c->TF.data(), c->TF.size() * 16)) != GW_OK) return s;
   if ((s = upload(c, &c->dTFp, c->TFp.data(), c->TFp.size() * 16)) != GW_OK) return s;
@@ -1181,16 +1207,18 @@ gw_status gw_screened_W_phi(gw_ctx* c, const gw_z* P0, int nq, gw_z* Pt, double*
 }
 
 // ------------------------------------------------------------- Eq. tilde_sigma2
-gw_status gw_self_energy(gw_ctx* c, const void* V, const gw_z* G, const gw_z* Pt, int q0, int nq,
-                         gw_z* Sig) {
-  if (!c) return GW_ERR_ARG;
-  if (!ready(c)) return fail(c, GW_ERR_STATE, "grids not built (gw_build_grids or gw_set_grids)");
-  if (q0 < 0 || nq < 0 || q0 + nq > c->nk) return fail(c, GW_ERR_ARG, "q range outside the mesh");
-  if (nq == 0) return GW_OK;
-  if (!V || !G || !Pt || !Sig) return fail(c, GW_ERR_ARG, "NULL array");
+// Contribution of one q at the tau nodes [tb, te); Gd is G in the chain's
+// storage type, Pt the [ntau][naux][naux] array of this q.
+// mirror (fp64): also the contribution of -q at the mirrored nodes, for P~ with
+// P~^{-q}(beta - tau) = P~^q(tau)^T = conj(P~^q(tau)) (P~ of a Hermitian G).
+// With V^{k+q,k} = V^{k,k+q}^H the long contraction of -q is then that of q,
+//   Vt^{-q}(beta - tau)[Q][k+q][b][j] = conj(Vt^q(tau)[Q][k][j][b]),
+// so only its producer and final contraction run:
+//   Sig^k(beta - tau) += -(1/nk) sum_{Q,b} X[k][Q][i][b] conj(Vt^q(tau)[Q][k][j][b]),
+//   X[k][Q][i][b] = sum_a V^{k,k+q}(Q)[i][a] G^{k+q}(beta - tau)[a][b].
+static gw_status se_nodes(gw_ctx* c, const char* Vd, const char* Gd, const gw_z* Pt, int q, int tb, int te,
+                          gw_z* Sig, bool mirror) {
   const int tc = c->tc;
-  if (!c->ws || c->ws_bytes < gw_workspace_bytes(c, GW_OP_SELF_ENERGY, tc))
-    return fail(c, GW_ERR_WORKSPACE, "self-energy workspace too small");
   const int nk = c->nk, nao = c->d.nao, naux = c->d.naux, nt = c->d.ntau;
   const long long n2 = c->n2, sv = c->sv;
   const long long S = (long long)nk * sv;
@@ -1199,104 +1227,151 @@ gw_status gw_self_energy(gw_ctx* c, const void* V, const gw_z* G, const gw_z* Pt
   const size_t ez = f32 ? 8 : 16;
   char* Vt = (char*)c->ws;
   char* L = (char*)c->ws + region_bytes(c, tc);
-  const char* Vd = (const char*)V;
+  const int t = f32 ? 1 : 0;
+  const bool kmajor = f32;   // layouts of Vt and L (see the final contraction)
+  const char* Aq = Vd + (size_t)q * nk * sv * ez;
+  for (int t0 = tb; t0 < te; t0 += tc) {
+    const int tcur = std::min(tc, te - t0);
+    // Vt[tl][Q][kk][b][j] = sum_Q' Pt[q][t0+tl][Q][Q'] V[q][kk][Q'][b][j]
+    // (fp64), or Vt[tl][kk][Q][b][j] (mixed): see the final contraction
+    if (sb) {
+      // bf16x3: rows Q of P~ (complex64 copy, K = Q' contiguous), columns
+      // (kk, b, j) of the V slab read in place (K = Q' with stride n2)
+      float2* Pc = (float2*)((char*)c->ws + 2 * region_bytes(c, tc) + 2 * gslot_bytes(c));
+      HIPCHK(c, to_c64_launch((const double2*)Pt + (long long)t0 * naux * naux, Pc,
+                              (long long)tcur * naux * naux, c->st));
+      SplitDesc d = split_desc();
+      d.A = Pc;
+      d.B = Aq; d.C = Vt;
+      d.M = naux; d.N = nk * (int)n2; d.K = naux; d.batch = tcur;
+      d.ta = 1; d.tb = 1; d.tc = 1;
+      d.am = aff(naux); d.aks = 1; d.ba = aff((long long)naux * naux);
+      d.bn = two((unsigned)n2, 1, sv); d.bks = n2; d.bb = aff(0);
+      d.cm = aff(n2); d.cn = two((unsigned)n2, 1, sv); d.bc = aff(S);
+      d.batch_fastest = 1;                    // every tau reads the same V slab
+      d.kchunk = kMixedChunk; d.nsplit = nsplit(c);
+      d.tag = KC_SE_CONTRACT;
+      gw_status s = run_split(c, d, Ext{0, (long long)tcur * naux * naux}, Ext{0, (long long)nk * sv},
+                              Ext{0, (long long)tcur * S});
+      if (s != GW_OK) return s;
+    } else {
+      GemmDesc g = gemm_desc();
+      g.A = (const double2*)Pt + (long long)t0 * naux * naux;
+      g.B = Aq; g.C = Vt;
+      g.M = naux; g.N = nk * (int)n2; g.K = naux; g.batch = tcur;
+      g.am = aff(naux); g.ak = aff(1);
+      g.bk = aff(n2); g.bn = two((unsigned)n2, 1, sv);
+      if (kmajor) { g.cm = aff(n2); g.cn = two((unsigned)n2, 1, sv); }
+      else { g.cm = aff((long long)nk * n2); g.cn = aff(1); }
+      g.ba = aff((long long)naux * naux); g.bb = aff(0); g.bc = aff(S);
+      g.ta = 0; g.tb = g.tc = t; g.f32 = t;
+      // groups of 8 tiles walk every tau: their V tiles and each tau's P~
+      // panels stay in L2 (measured at si-4x4x4: fetch 49 -> 29 GB per q,
+      // 25.6 vs 25.9 ms; groups of 16: 21 GB, 26.1 ms)
+      g.batch_fastest = 2;
+      g.group = 8;
+      g.tag = KC_SE_CONTRACT;
+      gw_status s = run(c, g, Ext{0, (long long)tcur * naux * naux}, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * S});
+      if (s != GW_OK) return s;
+    }
+    // L[tl][kk][Q][i][b] (fp64) or L[tl][kk][i][Q][b] (mixed)
+    //   = sum_a conj(V[q][kk][Q][a][i]) G[t0+tl][kk][a][b]
+    gw_status s;
+    GemmDesc g = gemm_desc();
+    g.A = Aq; g.B = Gd + (size_t)t0 * nk * n2 * ez; g.C = L;
+    g.M = naux * nao; g.N = tcur * nao; g.K = nao; g.batch = nk;
+    g.am = two(nao, 1, n2); g.ak = aff(nao); g.conjA = 1;
+    g.bk = aff(nao); g.bn = two(nao, 1, (long long)nk * n2);
+    g.cm = kmajor ? two(nao, (long long)naux * nao, nao) : aff(nao);
+    g.cn = two(nao, 1, S);
+    g.ba = aff(sv); g.bb = aff(n2); g.bc = aff(sv);
+    g.ta = g.tb = g.tc = t; g.f32 = t;
+    g.tag = KC_SE_PRODUCER;
+    if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * nk * n2}, Ext{0, (long long)tcur * S})) != GW_OK) return s;
+    // Sig[t0+tl][kk+q][i][j] += -(1/nk) sum_{Q,b} L(i, (Q, b)) Vt((Q, b), j)
+    // In the mixed layouts K = (Q, b) is contiguous in L and has stride nao
+    // in Vt, so the uniform-K loop applies (fp32 MFMA steps are short
+    // enough for the per-lane index carries of the other layout to show:
+    // 6.6 vs 8.8 ms per q); the fp64 contraction streams at the HBM read
+    // rate either way and is faster with its operands' k-points adjacent
+    // (7.3 vs 8.1 ms per q).
+    g = gemm_desc();
+    g.A = L; g.B = Vt; g.C = (double2*)Sig + (long long)t0 * nk * n2;
+    g.M = nao; g.N = nao; g.K = naux * nao; g.batch = tcur * nk;
+    if (kmajor) {
+      g.am = aff((long long)naux * nao); g.ak = aff(1);
+      g.bk = aff(nao); g.bn = aff(1);
+      g.bb = two(nk, sv, S);
+    } else {
+      g.am = aff(nao); g.ak = two(nao, 1, n2);
+      g.bk = two(nao, nao, (long long)nk * n2); g.bn = aff(1);
+      g.bb = two(nk, n2, S);
+    }
+    g.cm = aff(nao); g.cn = aff(1);
+    g.ba = two(nk, sv, S); g.bc = two(nk, 0, (long long)nk * n2);
+    g.tab = c->dplus + (size_t)q * nk; g.tmod = nk; g.tsC = n2;
+    g.alpha_r = -1.0 / nk;
+    g.beta_zero = 0; g.beta_r = 1.0;
+    g.ta = g.tb = t; g.tc = 0; g.f32 = t; g.kchunk = f32 ? kMixedChunk : 0;
+    g.tag = KC_SE_FINAL;
+    if ((s = run(c, g, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * nk * n2})) != GW_OK) return s;
+    if (!mirror) continue;
+    // -q at the mirrored nodes, X in the place of L; its rows run backwards in
+    // tau so that X[tl] belongs to Vt[tl]
+    g = gemm_desc();
+    g.A = Aq; g.B = Gd + (size_t)(nt - t0 - tcur) * nk * n2 * ez; g.C = L + (size_t)(tcur - 1) * S * ez;
+    g.M = naux * nao; g.N = tcur * nao; g.K = nao; g.batch = nk;
+    g.am = aff(nao); g.ak = aff(1);
+    g.bk = aff(nao); g.bn = two(nao, 1, (long long)nk * n2);
+    g.cm = aff(nao); g.cn = two(nao, 1, -S);
+    g.ba = aff(sv); g.bb = aff(0); g.bc = aff(sv);
+    g.tab = c->dplus + (size_t)q * nk; g.tmod = nk; g.tsB = n2;   // G^{k+q}
+    g.tag = KC_SE_PRODUCER;
+    if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * nk * n2},
+                 Ext{-(long long)(tcur - 1) * S, S})) != GW_OK) return s;
+    g = gemm_desc();
+    g.A = L; g.B = Vt; g.C = (double2*)Sig + (long long)(nt - 1 - t0) * nk * n2;
+    g.M = nao; g.N = nao; g.K = naux * nao; g.batch = tcur * nk;
+    g.am = aff(nao); g.ak = two(nao, 1, n2);
+    g.bk = two(nao, 1, (long long)nk * n2); g.bn = aff(nao); g.conjB = 1;
+    g.cm = aff(nao); g.cn = aff(1);
+    g.ba = two(nk, sv, S); g.bb = two(nk, n2, S); g.bc = two(nk, n2, -(long long)nk * n2);
+    g.alpha_r = -1.0 / nk;
+    g.beta_zero = 0; g.beta_r = 1.0;
+    g.tag = KC_SE_FINAL;
+    if ((s = run(c, g, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * S},
+                 Ext{-(long long)(tcur - 1) * nk * n2, (long long)nk * n2})) != GW_OK) return s;
+  }
+  return GW_OK;
+}
+
+// The contribution of the pair {q, -q} (of q alone when q = -q): half of the
+// nodes are enough for q = -q, whose mirrored nodes are its own.
+static gw_status se_pair(gw_ctx* c, const void* V, const gw_z* G, const gw_z* Pt, int q, gw_z* Sig) {
+  const int te = c->neg[q] == q ? c->d.ntau / 2 : c->d.ntau;
+  return se_nodes(c, (const char*)V, (const char*)G, Pt, q, 0, te, Sig, true);
+}
+
+gw_status gw_self_energy(gw_ctx* c, const void* V, const gw_z* G, const gw_z* Pt, int q0, int nq,
+                         gw_z* Sig) {
+  if (!c) return GW_ERR_ARG;
+  if (!ready(c)) return fail(c, GW_ERR_STATE, "grids not built (gw_build_grids or gw_set_grids)");
+  if (q0 < 0 || nq < 0 || q0 + nq > c->nk) return fail(c, GW_ERR_ARG, "q range outside the mesh");
+  if (nq == 0) return GW_OK;
+  if (!V || !G || !Pt || !Sig) return fail(c, GW_ERR_ARG, "NULL array");
+  if (!c->ws || c->ws_bytes < gw_workspace_bytes(c, GW_OP_SELF_ENERGY, c->tc))
+    return fail(c, GW_ERR_WORKSPACE, "self-energy workspace too small");
   const char* Gd = (const char*)G;
-  if (f32) {
+  if (lowp(c)) {
     void* Gc = nullptr;
     gw_status s = g_to_c64(c, ctx_work(c), G, &Gc);
     if (s != GW_OK) return s;
     Gd = (const char*)Gc;
   }
-  const int t = f32 ? 1 : 0;
-  const bool kmajor = f32;   // layouts of Vt and L (see the final contraction)
+  const long long per = (long long)c->d.ntau * c->d.naux * c->d.naux;
   for (int q = q0; q < q0 + nq; ++q) {
-    const char* Aq = Vd + (size_t)q * nk * sv * ez;
-    for (int t0 = 0; t0 < nt; t0 += tc) {
-      const int tcur = std::min(tc, nt - t0);
-      // Vt[tl][Q][kk][b][j] = sum_Q' Pt[q][t0+tl][Q][Q'] V[q][kk][Q'][b][j]
-      // (fp64), or Vt[tl][kk][Q][b][j] (mixed): see the final contraction
-      if (sb) {
-        // bf16x3: rows Q of P~ (complex64 copy, K = Q' contiguous), columns
-        // (kk, b, j) of the V slab read in place (K = Q' with stride n2)
-        float2* Pc = (float2*)((char*)c->ws + 2 * region_bytes(c, tc) + 2 * gslot_bytes(c));
-        HIPCHK(c, to_c64_launch((const double2*)Pt + ((long long)(q - q0) * nt + t0) * naux * naux, Pc,
-                                (long long)tcur * naux * naux, c->st));
-        SplitDesc d = split_desc();
-        d.A = Pc;
-        d.B = Aq; d.C = Vt;
-        d.M = naux; d.N = nk * (int)n2; d.K = naux; d.batch = tcur;
-        d.ta = 1; d.tb = 1; d.tc = 1;
-        d.am = aff(naux); d.aks = 1; d.ba = aff((long long)naux * naux);
-        d.bn = two((unsigned)n2, 1, sv); d.bks = n2; d.bb = aff(0);
-        d.cm = aff(n2); d.cn = two((unsigned)n2, 1, sv); d.bc = aff(S);
-        d.batch_fastest = 1;                    // every tau reads the same V slab
-        d.kchunk = kMixedChunk; d.nsplit = nsplit(c);
-        d.tag = KC_SE_CONTRACT;
-        gw_status s = run_split(c, d, Ext{0, (long long)tcur * naux * naux}, Ext{0, (long long)nk * sv},
-                                Ext{0, (long long)tcur * S});
-        if (s != GW_OK) return s;
-      } else {
-        GemmDesc g = gemm_desc();
-        g.A = (const double2*)Pt + ((long long)(q - q0) * nt + t0) * naux * naux;
-        g.B = Aq; g.C = Vt;
-        g.M = naux; g.N = nk * (int)n2; g.K = naux; g.batch = tcur;
-        g.am = aff(naux); g.ak = aff(1);
-        g.bk = aff(n2); g.bn = two((unsigned)n2, 1, sv);
-        if (kmajor) { g.cm = aff(n2); g.cn = two((unsigned)n2, 1, sv); }
-        else { g.cm = aff((long long)nk * n2); g.cn = aff(1); }
-        g.ba = aff((long long)naux * naux); g.bb = aff(0); g.bc = aff(S);
-        g.ta = 0; g.tb = g.tc = t; g.f32 = t;
-        // groups of 8 tiles walk every tau: their V tiles and each tau's P~
-        // panels stay in L2 (measured at si-4x4x4: fetch 49 -> 29 GB per q,
-        // 25.6 vs 25.9 ms; groups of 16: 21 GB, 26.1 ms)
-        g.batch_fastest = 2;
-        g.group = 8;
-        g.tag = KC_SE_CONTRACT;
-        gw_status s = run(c, g, Ext{0, (long long)tcur * naux * naux}, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * S});
-        if (s != GW_OK) return s;
-      }
-      // L[tl][kk][Q][i][b] (fp64) or L[tl][kk][i][Q][b] (mixed)
-      //   = sum_a conj(V[q][kk][Q][a][i]) G[t0+tl][kk][a][b]
-      gw_status s;
-      GemmDesc g = gemm_desc();
-      g.A = Aq; g.B = Gd + (size_t)t0 * nk * n2 * ez; g.C = L;
-      g.M = naux * nao; g.N = tcur * nao; g.K = nao; g.batch = nk;
-      g.am = two(nao, 1, n2); g.ak = aff(nao); g.conjA = 1;
-      g.bk = aff(nao); g.bn = two(nao, 1, (long long)nk * n2);
-      g.cm = kmajor ? two(nao, (long long)naux * nao, nao) : aff(nao);
-      g.cn = two(nao, 1, S);
-      g.ba = aff(sv); g.bb = aff(n2); g.bc = aff(sv);
-      g.ta = g.tb = g.tc = t; g.f32 = t;
-      g.tag = KC_SE_PRODUCER;
-      if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * nk * n2}, Ext{0, (long long)tcur * S})) != GW_OK) return s;
-      // Sig[t0+tl][kk+q][i][j] += -(1/nk) sum_{Q,b} L(i, (Q, b)) Vt((Q, b), j)
-      // In the mixed layouts K = (Q, b) is contiguous in L and has stride nao
-      // in Vt, so the uniform-K loop applies (fp32 MFMA steps are short
-      // enough for the per-lane index carries of the other layout to show:
-      // 6.6 vs 8.8 ms per q); the fp64 contraction streams at the HBM read
-      // rate either way and is faster with its operands' k-points adjacent
-      // (7.3 vs 8.1 ms per q).
-      g = gemm_desc();
-      g.A = L; g.B = Vt; g.C = (double2*)Sig + (long long)t0 * nk * n2;
-      g.M = nao; g.N = nao; g.K = naux * nao; g.batch = tcur * nk;
-      if (kmajor) {
-        g.am = aff((long long)naux * nao); g.ak = aff(1);
-        g.bk = aff(nao); g.bn = aff(1);
-        g.bb = two(nk, sv, S);
-      } else {
-        g.am = aff(nao); g.ak = two(nao, 1, n2);
-        g.bk = two(nao, nao, (long long)nk * n2); g.bn = aff(1);
-        g.bb = two(nk, n2, S);
-      }
-      g.cm = aff(nao); g.cn = aff(1);
-      g.ba = two(nk, sv, S); g.bc = two(nk, 0, (long long)nk * n2);
-      g.tab = c->dplus + (size_t)q * nk; g.tmod = nk; g.tsC = n2;
-      g.alpha_r = -1.0 / nk;
-      g.beta_zero = 0; g.beta_r = 1.0;
-      g.ta = g.tb = t; g.tc = 0; g.f32 = t; g.kchunk = f32 ? kMixedChunk : 0;
-      g.tag = KC_SE_FINAL;
-      if ((s = run(c, g, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * nk * n2})) != GW_OK) return s;
-    }
+    gw_status s = se_nodes(c, (const char*)V, Gd, Pt + (q - q0) * per, q, 0, c->d.ntau, Sig, false);
+    if (s != GW_OK) return s;
   }
   return GW_OK;
 }
@@ -1983,13 +2058,12 @@ static gw_status zero_z(gw_ctx* c, gw_z* Y, long long n) {
   return GW_OK;
 }
 
-// P~^q of G rebuilt for one q: P0^q(tau) -> P0^q(i Omega) (p.w0) ->
-// P~^q(i Omega) (p.w1) -> P~^q(tau) (p.ta).  phi (may be NULL) accumulates
-// this q's Phi~ term.
-static gw_status pt_one_q(gw_ctx* c, const void* V, const gw_z* G, int q, const PerQ& p, double* phi) {
+// P (P0^q(tau)) -> P0^q(i Omega) (p.w0) -> P~^q(i Omega) (p.w1) -> P~^q(tau),
+// in place.  phi (may be NULL) accumulates this q's Phi~ term.
+static gw_status pt_solve(gw_ctx* c, gw_z* P, const PerQ& p, double* phi) {
   gw_status s;
-  if ((s = pol_impl(c, ctx_work(c), V, G, G, q, 1, p.ta, false, false)) != GW_OK) return s;
-  if ((s = gw_tau_to_iw(c, GW_BOSON, p.ta, 1, (long long)c->d.naux * c->d.naux, p.w0)) != GW_OK) return s;
+  const long long nn = (long long)c->d.naux * c->d.naux;
+  if ((s = gw_tau_to_iw(c, GW_BOSON, P, 1, nn, p.w0)) != GW_OK) return s;
   if (phi) {
     double f = 0.0;
     if ((s = gw_screened_W_phi(c, p.w0, 1, p.w1, &f)) != GW_OK) return s;
@@ -1997,7 +2071,22 @@ static gw_status pt_one_q(gw_ctx* c, const void* V, const gw_z* G, int q, const 
   } else if ((s = gw_screened_W(c, p.w0, 1, p.w1)) != GW_OK) {
     return s;
   }
-  return gw_iw_to_tau(c, GW_BOSON, p.w1, 1, (long long)c->d.naux * c->d.naux, p.ta);
+  return gw_iw_to_tau(c, GW_BOSON, p.w1, 1, nn, P);
+}
+
+// P~^q of G rebuilt for one q into p.ta and p.w1.
+static gw_status pt_one_q(gw_ctx* c, const void* V, const gw_z* G, int q, const PerQ& p, double* phi) {
+  gw_status s = pol_impl(c, ctx_work(c), V, G, G, q, 1, p.ta, false, false);
+  return s != GW_OK ? s : pt_solve(c, p.ta, p, phi);
+}
+
+// Whether P~ of a G declared Hermitian is Hermitian at every node and mirrors
+// between q and -q, so that se_pair applies.  fp64 only (see pol_impl).
+// Measured with the polarization pairs in both, whole evaluation on a 3x3x3
+// mesh: 98.9 -> 83.3 ms (nao 16, naux 150, ntau 60), 721 -> 566 ms (nao 26,
+// naux 250, ntau 100); gw_sigma_jvp at the first of them 241 -> 147 ms.
+static bool pairs_ok(const gw_ctx* c, int bits) {
+  return !lowp(c) && c->sym_b && (c->herm & bits) == bits;
 }
 
 gw_status gw_sigma(gw_ctx* c, const void* V, const gw_z* G, gw_z* gamma, gw_z* Sinf, gw_z* Stau,
@@ -2017,6 +2106,7 @@ gw_status gw_sigma(gw_ctx* c, const void* V, const gw_z* G, gw_z* gamma, gw_z* S
   if ((s = gw_hf(c, V, G, gamma, Sinf)) != GW_OK) return s;
   if ((s = zero_z(c, Stau, (long long)c->d.ntau * nk * c->n2)) != GW_OK) return s;
   double ph = 0.0;
+  const bool pairs = pairs_ok(c, GW_HERM_FORWARD);
   if (stored) {
     if ((s = pol_impl(c, ctx_work(c), V, G, G, 0, nk, P_tau, false, false)) != GW_OK) return s;
     if ((s = gw_tau_to_iw(c, GW_BOSON, P_tau, nk, nn, P0_iw)) != GW_OK) return s;
@@ -2035,11 +2125,39 @@ gw_status gw_sigma(gw_ctx* c, const void* V, const gw_z* G, gw_z* gamma, gw_z* S
       }
     }
     if ((s = gw_iw_to_tau(c, GW_BOSON, Pt_iw, nk, nn, P_tau)) != GW_OK) return s;
-    if ((s = gw_self_energy(c, V, G, P_tau, 0, nk, Stau)) != GW_OK) return s;
-  } else {
+    if (!pairs) {
+      if ((s = gw_self_energy(c, V, G, P_tau, 0, nk, Stau)) != GW_OK) return s;
+    } else {
+      for (int q = 0; q < nk; ++q)
+        if (c->neg[q] >= q && (s = se_pair(c, V, G, P_tau + (size_t)q * c->d.ntau * nn, q, Stau)) != GW_OK)
+          return s;
+    }
+  } else if (lowp(c)) {
     for (int q = 0; q < nk; ++q) {
       if ((s = pt_one_q(c, V, G, q, p, phi ? &ph : nullptr)) != GW_OK) return s;
       if ((s = gw_self_energy(c, V, G, p.ta, q, 1, Stau)) != GW_OK) return s;
+    }
+  } else {
+    const bool herm = (c->herm & GW_HERM_FORWARD) != 0;
+    for (int q = 0; q < nk; ++q) {
+      const int m = c->neg[q];
+      if (m < q) continue;
+      if (m == q || pairs) {
+        double f = 0.0;
+        if ((s = pt_one_q(c, V, G, q, p, phi ? &f : nullptr)) != GW_OK) return s;
+        ph += m == q ? f : 2.0 * f;      // -q has the same Phi~ term
+        s = pairs ? se_pair(c, V, G, p.ta, q, Stau) : gw_self_energy(c, V, G, p.ta, q, 1, Stau);
+        if (s != GW_OK) return s;
+        continue;
+      }
+      // P0^{-q} by transposition, then one q after the other
+      if ((s = pol_nodes(c, ctx_work(c), (const char*)V, (const char*)G, (const char*)G, q, 0, c->d.ntau, p.ta,
+                         false, herm)) != GW_OK) return s;
+      if ((s = pol_finish(c, p.ta, p.tb, 0, c->d.ntau, herm)) != GW_OK) return s;
+      if ((s = pt_solve(c, p.ta, p, phi ? &ph : nullptr)) != GW_OK) return s;
+      if ((s = gw_self_energy(c, V, G, p.ta, q, 1, Stau)) != GW_OK) return s;
+      if ((s = pt_solve(c, p.tb, p, phi ? &ph : nullptr)) != GW_OK) return s;
+      if ((s = gw_self_energy(c, V, G, p.tb, m, 1, Stau)) != GW_OK) return s;
     }
   }
   if (phi) {
@@ -2072,18 +2190,35 @@ gw_status gw_sigma_jvp(gw_ctx* c, const void* V, const gw_z* G, const gw_z* Pt_t
   // dSigma_inf = HF[gamma(dG)] (linear in G)
   if ((s = gw_hf(c, V, dG, nullptr, dSinf)) != GW_OK) return s;
   if ((s = zero_z(c, dStau, (long long)nt * nk * c->n2)) != GW_OK) return s;
+  const bool pairs = pairs_ok(c, GW_HERM_FORWARD | GW_HERM_TWO_SLOT);
   for (int q = 0; q < nk; ++q) {
     const gw_z* pt = stored ? Pt_tau + (size_t)q * nt * nn : p.ta;
     const gw_z* pw = stored ? Pt_iw + (size_t)q * nwb * nn : p.w1;
+    if (pairs && c->neg[q] < q) continue;
     if (!stored && (s = pt_one_q(c, V, G, q, p, nullptr)) != GW_OK) return s;
     // dP0 = P0[dG, G] + P0[G, dG]
-    if ((s = pol_impl(c, ctx_work(c), V, dG, G, q, 1, p.tb, false, true)) != GW_OK) return s;
-    if ((s = pol_impl(c, ctx_work(c), V, G, dG, q, 1, p.tb, true, true)) != GW_OK) return s;
+    if (pairs) {
+      // the sum is symmetric in its slots, so it mirrors as P0[G, G] does
+      const char *Vd = (const char*)V, *Gd = (const char*)G, *dGd = (const char*)dG;
+      const bool self = c->neg[q] == q;
+      const int te = self ? nt / 2 : nt;
+      if ((s = pol_nodes(c, ctx_work(c), Vd, dGd, Gd, q, 0, te, p.tb, false, true)) != GW_OK) return s;
+      if ((s = pol_nodes(c, ctx_work(c), Vd, Gd, dGd, q, 0, te, p.tb, true, true)) != GW_OK) return s;
+      if ((s = pol_finish(c, p.tb, self ? p.tb : nullptr, 0, te, true)) != GW_OK) return s;
+    } else {
+      if ((s = pol_impl(c, ctx_work(c), V, dG, G, q, 1, p.tb, false, true)) != GW_OK) return s;
+      if ((s = pol_impl(c, ctx_work(c), V, G, dG, q, 1, p.tb, true, true)) != GW_OK) return s;
+    }
     // dP~(i Omega) = (I + P~) dP0(i Omega) (I + P~)
     if ((s = gw_tau_to_iw(c, GW_BOSON, p.tb, 1, nn, p.w2)) != GW_OK) return s;
     if ((s = gw_screened_W_lin(c, pw, p.w2, 1, 0, p.w3)) != GW_OK) return s;
     if ((s = gw_iw_to_tau(c, GW_BOSON, p.w3, 1, nn, p.tb)) != GW_OK) return s;
     // dSigma~ += Sigma~[dP~, G] + Sigma~[P~, dG]
+    if (pairs) {
+      if ((s = se_pair(c, V, G, p.tb, q, dStau)) != GW_OK) return s;
+      if ((s = se_pair(c, V, dG, pt, q, dStau)) != GW_OK) return s;
+      continue;
+    }
     if ((s = gw_self_energy(c, V, G, p.tb, q, 1, dStau)) != GW_OK) return s;
     if ((s = gw_self_energy(c, V, dG, pt, q, 1, dStau)) != GW_OK) return s;
   }
