@@ -5,18 +5,19 @@ import os
 import shutil
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgw.so")
-SOURCES = ["gw_kernels.hip", "gw_api.hip", "grids.cpp", "ir.cpp"]
+SOURCES = ["gw_kernels.hip", "gw_sandwich.hip", "gw_api.hip", "grids.cpp", "ir.cpp"]
 
 
 def source_hash():
     """sha256 of the kernel and ABI sources (names counter summaries to a build)."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("gw_kernels.hip", "gw_kernels.h", "gw_api.hip"):
+    for f in ("gw_kernels.hip", "gw_sandwich.hip", "gw_kernels.h", "gw_device.h", "gw_api.hip"):
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
@@ -31,16 +32,25 @@ def hipcc():
 
 def build(verbose=False, arch="gfx950"):
     out_tmp = LIB + ".tmp"
-    cmd = [hipcc(), f"--offload-arch={arch}", "-O3", "-std=c++17", "-fPIC", "-shared",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           # MFMA accumulators in arch VGPRs: avoids per-iteration AGPR copies
-           "-mllvm", "-amdgpu-mfma-vgpr-form",
-           "-Wno-unused-result", "-I", os.path.join(HERE, "..", "include"),
-           "-o", out_tmp] + [os.path.join(CSRC, s) for s in SOURCES]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    msg = "\n".join(l for l in (r.stdout + r.stderr).splitlines()
-                    if "packed-fp32-ops" not in l)
-    if r.returncode != 0:
+    flags = [f"--offload-arch={arch}", "-O3", "-std=c++17", "-fPIC",
+             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+             # MFMA accumulators in arch VGPRs: avoids per-iteration AGPR copies
+             "-mllvm", "-amdgpu-mfma-vgpr-form",
+             "-Wno-unused-result", "-I", os.path.join(HERE, "..", "include")]
+    with tempfile.TemporaryDirectory() as tmp:
+        # one compiler process per source, side by side
+        objs = [os.path.join(tmp, f + ".o") for f in SOURCES]
+        procs = [subprocess.Popen([hipcc(), *flags, "-c", os.path.join(CSRC, f), "-o", o], stdout=subprocess.PIPE,
+                                  stderr=subprocess.STDOUT, text=True) for f, o in zip(SOURCES, objs)]
+        out = [p.communicate()[0] for p in procs]
+        failed = any(p.returncode for p in procs)
+        if not failed:
+            r = subprocess.run([hipcc(), f"--offload-arch={arch}", "-fPIC", "-shared", "-o", out_tmp] + objs,
+                               capture_output=True, text=True)
+            out.append(r.stdout + r.stderr)
+            failed = r.returncode != 0
+    msg = "\n".join(l for l in "".join(out).splitlines() if "packed-fp32-ops" not in l)
+    if failed:
         raise RuntimeError("hipcc failed:\n" + msg)
     if verbose and msg.strip():
         print(msg, file=sys.stderr)

@@ -268,6 +268,29 @@ gw_status run_split(gw_ctx* c, const SplitDesc& d, Ext eA, Ext eB, Ext eC) {
   return prof_end(c, d.tag, e0, 8.0 * outs * d.K * d.batch);
 }
 
+// The triple products (nao x nao matrices) with their profiling class; 6 real
+// flops per complex multiply-add (three real products).
+gw_status sand_prod(gw_ctx* c, SandProd d, int tag) {
+  d.nk = c->nk; d.naux = c->d.naux; d.nao = c->d.nao;
+  d.svk = c->sv;
+  hipEvent_t e0 = nullptr;
+  gw_status s = prof_begin(c, tag, &e0);
+  if (s != GW_OK) return s;
+  hipError_t e = sand_prod_launch(d, c->st);
+  if (e != hipSuccess) return fail(c, GW_ERR_DEVICE, std::string("sand_prod: ") + hipGetErrorString(e));
+  return prof_end(c, tag, e0, 12.0 * d.nt * d.nk * c->sv * c->d.nao);
+}
+
+gw_status sand_sum(gw_ctx* c, SandSum d, int tag) {
+  d.nk = c->nk; d.naux = c->d.naux; d.nao = c->d.nao;
+  hipEvent_t e0 = nullptr;
+  gw_status s = prof_begin(c, tag, &e0);
+  if (s != GW_OK) return s;
+  hipError_t e = sand_sum_launch(d, c->st);
+  if (e != hipSuccess) return fail(c, GW_ERR_DEVICE, std::string("sand_sum: ") + hipGetErrorString(e));
+  return prof_end(c, tag, e0, 12.0 * d.nt * d.nk * c->sv * c->d.nao);
+}
+
 gw_status read_flag(gw_ctx* c, const char* what) {
   int f = 0;
   HIPCHK(c, hipMemcpyAsync(&f, c->dflag, sizeof(int), hipMemcpyDeviceToHost, c->st));
@@ -948,9 +971,12 @@ static gw_status pol_split_chunk(gw_ctx* c, const char* Aq, const char* Gd, cons
 // The tau nodes [tb, te) of P0^q, written to P0, the
 // [ntau][naux][naux] array of this q; Gd and Gbd are the two G slots in
 // the chain's storage type.  With herm only the output tiles on and above the
-// diagonal are valid afterwards (pol_finish fills the rest).
+// diagonal are valid afterwards (pol_finish fills the rest).  fp64: Gd2 and
+// Gbd2 (may be NULL) are a second pair of slots, added to the first one's
+// term before the long contraction.
 static gw_status pol_nodes(gw_ctx* c, const Work& w, const char* Vd, const char* Gd, const char* Gbd, int q,
-                           int tb, int te, gw_z* P0, bool accumulate, bool herm);
+                           int tb, int te, gw_z* P0, bool accumulate, bool herm, const char* Gd2 = nullptr,
+                           const char* Gbd2 = nullptr);
 
 // Completes the nodes [tb, te) of one q: the lower triangle in Hermitian
 // mode, and with M0 the mirrored nodes M0[ntau-1-i] = P0[i]^T of -q.
@@ -1018,7 +1044,8 @@ static gw_status pol_impl(gw_ctx* c, const Work& w, const void* V, const gw_z* G
 }
 
 static gw_status pol_nodes(gw_ctx* c, const Work& w, const char* Vd, const char* Gd, const char* Gbd, int q,
-                           int tb, int te, gw_z* P0, bool accumulate, bool herm) {
+                           int tb, int te, gw_z* P0, bool accumulate, bool herm, const char* Gd2,
+                           const char* Gbd2) {
   const int tc = w.tc;
   const int nk = c->nk, nao = c->d.nao, naux = c->d.naux, nt = c->d.ntau;
   const long long n2 = c->n2, sv = c->sv;
@@ -1028,13 +1055,47 @@ static gw_status pol_nodes(gw_ctx* c, const Work& w, const char* Vd, const char*
   const size_t ez = f32 ? 8 : 16;                        // bytes of V / X / Zt / G elements
   char* X = w.base;
   char* Z = w.base + region_bytes(c, tc);
-  const int t = f32 ? 1 : 0;
   const char* Aq = Vd + (size_t)q * nk * sv * ez;
   for (int t0 = tb; t0 < te; t0 += tc) {
     const int tcur = std::min(tc, te - t0);
     if (sb) {
       gw_status s = pol_split_chunk(c, Aq, Gd, Gbd, X, Z, q, 0, t0, tcur, tc, P0, accumulate, herm);
       if (s != GW_OK) return s;
+      continue;
+    }
+    if (!f32) {
+      // Y[tl][k][Q][c][b] = sum_{d,a} Gb[nt-1-t0-tl][k][c][d] V[q][k][Q][d][a] G[t0+tl][k+q][a][b]
+      // P0[t0+tl][Q][Q'] = -(ns/nk) sum_{k,c,b} Y[tl][k][Q][c][b] conj(V[q][k][Q'][c][b])
+      // Both G on one side: one tau array is written and read instead of two
+      // (V G and Gb conj(V)), and the other operand is the V slab that every
+      // tau shares.
+      const long long gs = (long long)nk * n2;
+      SandProd p{};
+      p.V = (const double2*)Aq; p.Y = (double2*)X; p.tab = c->dplus + (size_t)q * nk;
+      p.nt = tcur; p.tsY = S; p.tabR = 1; p.tsL = -gs; p.tsR = gs;
+      p.L = (const double2*)Gbd + (nt - 1 - t0) * gs;
+      p.R = (const double2*)Gd + t0 * gs;
+      gw_status s = sand_prod(c, p, KC_POL_PRODUCER);
+      if (s != GW_OK) return s;
+      if (Gd2) {
+        p.L = (const double2*)Gbd2 + (nt - 1 - t0) * gs;
+        p.R = (const double2*)Gd2 + t0 * gs;
+        p.accumulate = 1;
+        if ((s = sand_prod(c, p, KC_POL_PRODUCER)) != GW_OK) return s;
+      }
+      GemmDesc g = gemm_desc();
+      g.A = X; g.B = Aq; g.C = (double2*)P0 + (long long)t0 * naux * naux;
+      g.M = naux; g.N = naux; g.K = nk * (int)n2; g.batch = tcur;
+      g.am = aff(n2); g.ak = two((unsigned)n2, 1, sv);
+      g.bk = two((unsigned)n2, 1, sv); g.bn = aff(n2); g.conjB = 1;
+      g.cm = aff(naux); g.cn = aff(1);
+      g.ba = aff(S); g.bb = aff(0); g.bc = aff((long long)naux * naux);
+      g.alpha_r = -(double)c->d.ns / nk;
+      if (accumulate) { g.beta_zero = 0; g.beta_r = 1.0; }
+      g.tri = herm ? 1 : 0;
+      g.tag = KC_POL_CONTRACT;
+      if ((s = run(c, g, Ext{0, (long long)tcur * S}, Ext{0, S}, Ext{0, (long long)tcur * naux * naux})) != GW_OK)
+        return s;
       continue;
     }
     // X[tl][k][Q][d][b] = sum_a V[q][k][Q][d][a] G[t0+tl][k+q][a][b]
@@ -1046,7 +1107,7 @@ static gw_status pol_nodes(gw_ctx* c, const Work& w, const char* Vd, const char*
     g.cm = aff(nao); g.cn = two(nao, 1, S);
     g.ba = aff(sv); g.bb = aff(0); g.bc = aff(sv);
     g.tab = c->dplus + (size_t)q * nk; g.tmod = nk; g.tsB = n2;   // G^{k+q}
-    g.ta = g.tb = g.tc = t; g.f32 = t;
+    g.ta = g.tb = g.tc = g.f32 = 1;
     g.tag = KC_POL_PRODUCER;
     gw_status s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * nk * n2}, Ext{0, (long long)tc * S});
     if (s != GW_OK) return s;
@@ -1062,7 +1123,7 @@ static gw_status pol_nodes(gw_ctx* c, const Work& w, const char* Vd, const char*
     g.bk = aff(nao); g.bn = two(nao, 1, n2); g.conjB = 1;
     g.cm = two(nao, nao, -S); g.cn = two(nao, 1, n2);
     g.ba = aff(n2); g.bb = aff(sv); g.bc = aff(sv);
-    g.ta = g.tb = g.tc = t; g.f32 = t;
+    g.ta = g.tb = g.tc = g.f32 = 1;
     g.tag = KC_POL_PRODUCER;
     if ((s = run(c, g, Ext{0, (long long)tcur * nk * n2}, Ext{0, (long long)nk * sv},
                  Ext{-(long long)(tcur - 1) * S, (long long)(tc - tcur + 1) * S})) != GW_OK) return s;
@@ -1076,7 +1137,7 @@ static gw_status pol_nodes(gw_ctx* c, const Work& w, const char* Vd, const char*
     g.ba = aff(S); g.bb = aff(S); g.bc = aff((long long)naux * naux);
     g.alpha_r = -(double)c->d.ns / nk;
     if (accumulate) { g.beta_zero = 0; g.beta_r = 1.0; }
-    g.ta = g.tb = t; g.tc = 0; g.f32 = t; g.kchunk = f32 ? kMixedChunk : 0;
+    g.ta = g.tb = g.f32 = 1; g.tc = 0; g.kchunk = kMixedChunk;
     g.tag = KC_POL_CONTRACT;
     g.tri = herm ? 1 : 0;
     if ((s = run(c, g, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * naux * naux})) != GW_OK) return s;
@@ -1228,7 +1289,6 @@ static gw_status se_nodes(gw_ctx* c, const char* Vd, const char* Gd, const gw_z*
   char* Vt = (char*)c->ws;
   char* L = (char*)c->ws + region_bytes(c, tc);
   const int t = f32 ? 1 : 0;
-  const bool kmajor = f32;   // layouts of Vt and L (see the final contraction)
   const char* Aq = Vd + (size_t)q * nk * sv * ez;
   for (int t0 = tb; t0 < te; t0 += tc) {
     const int tcur = std::min(tc, te - t0);
@@ -1261,7 +1321,7 @@ static gw_status se_nodes(gw_ctx* c, const char* Vd, const char* Gd, const gw_z*
       g.M = naux; g.N = nk * (int)n2; g.K = naux; g.batch = tcur;
       g.am = aff(naux); g.ak = aff(1);
       g.bk = aff(n2); g.bn = two((unsigned)n2, 1, sv);
-      if (kmajor) { g.cm = aff(n2); g.cn = two((unsigned)n2, 1, sv); }
+      if (f32) { g.cm = aff(n2); g.cn = two((unsigned)n2, 1, sv); }
       else { g.cm = aff((long long)nk * n2); g.cn = aff(1); }
       g.ba = aff((long long)naux * naux); g.bb = aff(0); g.bc = aff(S);
       g.ta = 0; g.tb = g.tc = t; g.f32 = t;
@@ -1274,73 +1334,58 @@ static gw_status se_nodes(gw_ctx* c, const char* Vd, const char* Gd, const gw_z*
       gw_status s = run(c, g, Ext{0, (long long)tcur * naux * naux}, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * S});
       if (s != GW_OK) return s;
     }
-    // L[tl][kk][Q][i][b] (fp64) or L[tl][kk][i][Q][b] (mixed)
-    //   = sum_a conj(V[q][kk][Q][a][i]) G[t0+tl][kk][a][b]
     gw_status s;
+    if (!f32) {
+      // Sig[t0+tl][kk+q] += -(1/nk) sum_Q V[q][kk][Q]^H G[t0+tl][kk] Vt[tl][Q][kk]
+      const long long gs = (long long)nk * n2;
+      SandSum x{};
+      x.A = Aq; x.skA = sv; x.sqA = n2;
+      x.B = Vt; x.tsB = S; x.skB = n2; x.sqB = gs;
+      x.tab = c->dplus + (size_t)q * nk;
+      x.nt = tcur; x.alpha = -1.0 / nk; x.accumulate = 1;
+      x.part = (double2*)L; x.part_elems = (long long)tc * S;
+      x.G = (const double2*)Gd + t0 * gs; x.tsG = gs;
+      x.O = (double2*)Sig + t0 * gs; x.tsO = gs; x.tabO = 1;
+      if ((s = sand_sum(c, x, KC_SE_FINAL)) != GW_OK) return s;
+      if (!mirror) continue;
+      // -q at the mirrored nodes:
+      // Sig[nt-1-t0-tl][kk] += -(1/nk) sum_Q V[q][kk][Q] G[nt-1-t0-tl][kk+q] Vt[tl][Q][kk]^H
+      x.bh = 1;
+      x.G = (const double2*)Gd + (nt - 1 - t0) * gs; x.tsG = -gs; x.tabG = 1;
+      x.O = (double2*)Sig + (nt - 1 - t0) * gs; x.tsO = -gs; x.tabO = 0;
+      if ((s = sand_sum(c, x, KC_SE_FINAL)) != GW_OK) return s;
+      continue;
+    }
+    // L[tl][kk][i][Q][b] = sum_a conj(V[q][kk][Q][a][i]) G[t0+tl][kk][a][b]
     GemmDesc g = gemm_desc();
     g.A = Aq; g.B = Gd + (size_t)t0 * nk * n2 * ez; g.C = L;
     g.M = naux * nao; g.N = tcur * nao; g.K = nao; g.batch = nk;
     g.am = two(nao, 1, n2); g.ak = aff(nao); g.conjA = 1;
     g.bk = aff(nao); g.bn = two(nao, 1, (long long)nk * n2);
-    g.cm = kmajor ? two(nao, (long long)naux * nao, nao) : aff(nao);
+    g.cm = two(nao, (long long)naux * nao, nao);
     g.cn = two(nao, 1, S);
     g.ba = aff(sv); g.bb = aff(n2); g.bc = aff(sv);
-    g.ta = g.tb = g.tc = t; g.f32 = t;
+    g.ta = g.tb = g.tc = g.f32 = 1;
     g.tag = KC_SE_PRODUCER;
     if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * nk * n2}, Ext{0, (long long)tcur * S})) != GW_OK) return s;
     // Sig[t0+tl][kk+q][i][j] += -(1/nk) sum_{Q,b} L(i, (Q, b)) Vt((Q, b), j)
-    // In the mixed layouts K = (Q, b) is contiguous in L and has stride nao
-    // in Vt, so the uniform-K loop applies (fp32 MFMA steps are short
-    // enough for the per-lane index carries of the other layout to show:
-    // 6.6 vs 8.8 ms per q); the fp64 contraction streams at the HBM read
-    // rate either way and is faster with its operands' k-points adjacent
-    // (7.3 vs 8.1 ms per q).
+    // K = (Q, b) is contiguous in L and has stride nao in Vt, so the uniform-K
+    // loop applies (fp32 MFMA steps are short enough for the per-lane index
+    // carries of the fp64 layout to show: 6.6 vs 8.8 ms per q)
     g = gemm_desc();
     g.A = L; g.B = Vt; g.C = (double2*)Sig + (long long)t0 * nk * n2;
     g.M = nao; g.N = nao; g.K = naux * nao; g.batch = tcur * nk;
-    if (kmajor) {
-      g.am = aff((long long)naux * nao); g.ak = aff(1);
-      g.bk = aff(nao); g.bn = aff(1);
-      g.bb = two(nk, sv, S);
-    } else {
-      g.am = aff(nao); g.ak = two(nao, 1, n2);
-      g.bk = two(nao, nao, (long long)nk * n2); g.bn = aff(1);
-      g.bb = two(nk, n2, S);
-    }
+    g.am = aff((long long)naux * nao); g.ak = aff(1);
+    g.bk = aff(nao); g.bn = aff(1);
+    g.bb = two(nk, sv, S);
     g.cm = aff(nao); g.cn = aff(1);
     g.ba = two(nk, sv, S); g.bc = two(nk, 0, (long long)nk * n2);
     g.tab = c->dplus + (size_t)q * nk; g.tmod = nk; g.tsC = n2;
     g.alpha_r = -1.0 / nk;
     g.beta_zero = 0; g.beta_r = 1.0;
-    g.ta = g.tb = t; g.tc = 0; g.f32 = t; g.kchunk = f32 ? kMixedChunk : 0;
+    g.ta = g.tb = g.f32 = 1; g.tc = 0; g.kchunk = kMixedChunk;
     g.tag = KC_SE_FINAL;
     if ((s = run(c, g, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * nk * n2})) != GW_OK) return s;
-    if (!mirror) continue;
-    // -q at the mirrored nodes, X in the place of L; its rows run backwards in
-    // tau so that X[tl] belongs to Vt[tl]
-    g = gemm_desc();
-    g.A = Aq; g.B = Gd + (size_t)(nt - t0 - tcur) * nk * n2 * ez; g.C = L + (size_t)(tcur - 1) * S * ez;
-    g.M = naux * nao; g.N = tcur * nao; g.K = nao; g.batch = nk;
-    g.am = aff(nao); g.ak = aff(1);
-    g.bk = aff(nao); g.bn = two(nao, 1, (long long)nk * n2);
-    g.cm = aff(nao); g.cn = two(nao, 1, -S);
-    g.ba = aff(sv); g.bb = aff(0); g.bc = aff(sv);
-    g.tab = c->dplus + (size_t)q * nk; g.tmod = nk; g.tsB = n2;   // G^{k+q}
-    g.tag = KC_SE_PRODUCER;
-    if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * nk * n2},
-                 Ext{-(long long)(tcur - 1) * S, S})) != GW_OK) return s;
-    g = gemm_desc();
-    g.A = L; g.B = Vt; g.C = (double2*)Sig + (long long)(nt - 1 - t0) * nk * n2;
-    g.M = nao; g.N = nao; g.K = naux * nao; g.batch = tcur * nk;
-    g.am = aff(nao); g.ak = two(nao, 1, n2);
-    g.bk = two(nao, 1, (long long)nk * n2); g.bn = aff(nao); g.conjB = 1;
-    g.cm = aff(nao); g.cn = aff(1);
-    g.ba = two(nk, sv, S); g.bb = two(nk, n2, S); g.bc = two(nk, n2, -(long long)nk * n2);
-    g.alpha_r = -1.0 / nk;
-    g.beta_zero = 0; g.beta_r = 1.0;
-    g.tag = KC_SE_FINAL;
-    if ((s = run(c, g, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * S},
-                 Ext{-(long long)(tcur - 1) * nk * n2, (long long)nk * n2})) != GW_OK) return s;
   }
   return GW_OK;
 }
@@ -1402,6 +1447,28 @@ gw_status gw_density(gw_ctx* c, const gw_z* G, const gw_z* S, gw_z* gamma, doubl
 }
 
 // ------------------------------------------------------------- Eqs. HF_J, HF_K
+// The exchange sums over q: with fold, O[k] += -(1/nk) sum_{q,Q} V^{k,k+q} X[k+q] V^H;
+// otherwise O[k+q] += -(1/nk) sum_{q,Q} V^H X[k] V.  T holds nk naux nao^2
+// numbers; as many q at once as leave room for their partial sums.
+static gw_status exchange(gw_ctx* c, const char* Vd, const double2* X, double2* T, double2* O, bool fold) {
+  const int nk = c->nk, tv = lowp(c) ? 1 : 0;
+  const size_t ez = tv ? 8 : 16;
+  const int qb = fold ? std::min(nk, c->d.naux) : 1;
+  for (int q0 = 0; q0 < nk; q0 += qb) {
+    SandSum x{};
+    x.A = x.B = Vd + (size_t)q0 * nk * c->sv * ez;
+    x.tsA = x.tsB = nk * c->sv; x.skA = x.skB = c->sv; x.sqA = x.sqB = c->n2;
+    x.tv = tv; x.nt = std::min(qb, nk - q0); x.alpha = -1.0 / nk; x.accumulate = 1;
+    x.tab = c->dplus + (size_t)q0 * nk; x.tstab = nk;
+    x.G = X; x.O = O; x.part = T; x.part_elems = nk * c->sv;
+    if (fold) { x.bh = 1; x.tabG = 1; x.fold_t = 1; }
+    else x.tabO = 1;
+    gw_status s = sand_sum(c, x, KC_HF);
+    if (s != GW_OK) return s;
+  }
+  return GW_OK;
+}
+
 gw_status gw_hf(gw_ctx* c, const void* V, const gw_z* G, gw_z* gamma_out, gw_z* Sinf) {
   if (!c) return GW_ERR_ARG;
   if (!ready(c)) return fail(c, GW_ERR_STATE, "grids not built (gw_build_grids or gw_set_grids)");
@@ -1420,18 +1487,12 @@ gw_status gw_hf(gw_ctx* c, const void* V, const gw_z* G, gw_z* gamma_out, gw_z* 
   gw_status s = gamma_of(c, G, gam);
   if (s != GW_OK) return s;
   // v[Q] = (ns/nk) sum_{k',b,a} V[0][k'][Q][b][a] gamma[k'][a][b]
-  GemmDesc g = gemm_desc();
-  g.A = Vd; g.B = gam; g.C = vq;
-  g.M = naux; g.N = 1; g.K = nk * (int)n2;
-  g.am = aff(n2); g.ak = two((unsigned)n2, 1, sv);
-  g.bk = three(nao, nao, nao, 1, n2); g.bn = aff(0);
-  g.cm = aff(1); g.cn = aff(0);
-  g.alpha_r = (double)c->d.ns / nk;
-  g.ta = tv;
-  g.tag = KC_HF;
-  if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)nk * n2}, Ext{0, (long long)naux})) != GW_OK) return s;
+  hipEvent_t e0 = nullptr;
+  if ((s = prof_begin(c, KC_HF, &e0)) != GW_OK) return s;
+  HIPCHK(c, vdot_launch(Vd, tv, gam, vq, nk, naux, nao, (double)c->d.ns / nk, false, true, c->st));
+  if ((s = prof_end(c, KC_HF, e0, 8.0 * nk * sv)) != GW_OK) return s;
   // J[k][e] = sum_Q v[Q] V[0][k][Q][e]
-  g = gemm_desc();
+  GemmDesc g = gemm_desc();
   g.A = vq; g.B = Vd; g.C = (double2*)Sinf;
   g.M = 1; g.N = nk * (int)n2; g.K = naux;
   g.am = aff(0); g.ak = aff(1);
@@ -1440,34 +1501,9 @@ gw_status gw_hf(gw_ctx* c, const void* V, const gw_z* G, gw_z* gamma_out, gw_z* 
   g.tb = tv;
   g.tag = KC_HF;
   if ((s = run(c, g, Ext{0, (long long)naux}, Ext{0, (long long)nk * sv}, Ext{0, (long long)nk * n2})) != GW_OK) return s;
-  for (int q = 0; q < nk; ++q) {
-    const char* Aq = Vd + (size_t)q * nk * sv * ez;
-    // T1[k][Q][i][b] = sum_a V[q][k][Q][i][a] gamma[k+q][a][b]
-    g = gemm_desc();
-    g.A = Aq; g.B = gam; g.C = T1;
-    g.M = naux * nao; g.N = nao; g.K = nao; g.batch = nk;
-    g.am = aff(nao); g.ak = aff(1); g.bk = aff(nao); g.bn = aff(1);
-    g.cm = aff(nao); g.cn = aff(1);
-    g.ba = aff(sv); g.bb = aff(0); g.bc = aff(sv);
-    g.tab = c->dplus + (size_t)q * nk; g.tmod = nk; g.tsB = n2;
-    g.ta = tv;
-    g.tag = KC_HF;
-    if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)nk * n2}, Ext{0, (long long)nk * sv})) != GW_OK) return s;
-    // Sinf[k][i][j] += -(1/nk) sum_{Q,b} T1[k][Q][i][b] conj(V[q][k][Q][j][b])
-    g = gemm_desc();
-    g.A = T1; g.B = Aq; g.C = (double2*)Sinf;
-    g.M = nao; g.N = nao; g.K = naux * nao; g.batch = nk;
-    g.am = aff(nao); g.ak = two(nao, 1, n2);
-    g.bk = two(nao, 1, n2); g.bn = aff(nao); g.conjB = 1;
-    g.cm = aff(nao); g.cn = aff(1);
-    g.ba = aff(sv); g.bb = aff(sv); g.bc = aff(n2);
-    g.alpha_r = -1.0 / nk;
-    g.beta_zero = 0; g.beta_r = 1.0;
-    g.tb = tv;
-    g.tag = KC_HF;
-    if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)nk * sv}, Ext{0, (long long)nk * n2})) != GW_OK) return s;
-  }
-  return GW_OK;
+  // Sinf[k] += -(1/nk) sum_{q,Q} V[q][k][Q] gamma[k+q] V[q][k][Q]^H: one sum
+  // over Q per (q, k), then the sum over q
+  return exchange(c, Vd, gam, T1, (double2*)Sinf, true);
 }
 
 // ------------------------------------------------------------- Eq. Dyson
@@ -1846,16 +1882,12 @@ gw_status gw_hf_vjp(gw_ctx* c, const void* V, const gw_z* Sbar, gw_z* Gbar) {
   double2* gb = (double2*)((char*)c->ws + align256((size_t)nk * sv * 16));
   double2* vb = (double2*)((char*)gb + align256((size_t)nk * n2 * 16));
   // vbar[Q] = sum_{k,e} conj(V[0][k][Q][e]) Sbar[k][e]
-  GemmDesc g = gemm_desc();
-  g.A = Vd; g.B = Sbar; g.C = vb;
-  g.M = naux; g.N = 1; g.K = nk * (int)n2;
-  g.am = aff(n2); g.ak = two((unsigned)n2, 1, sv); g.conjA = 1;
-  g.bk = aff(1); g.bn = aff(0); g.cm = aff(1); g.cn = aff(0);
-  g.ta = tv;
-  g.tag = KC_HF;
-  if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)nk * n2}, Ext{0, (long long)naux})) != GW_OK) return s;
+  hipEvent_t e0 = nullptr;
+  if ((s = prof_begin(c, KC_HF, &e0)) != GW_OK) return s;
+  HIPCHK(c, vdot_launch(Vd, tv, (const double2*)Sbar, vb, nk, naux, nao, 1.0, true, false, c->st));
+  if ((s = prof_end(c, KC_HF, e0, 8.0 * nk * sv)) != GW_OK) return s;
   // gbar[k'][a][b] = (ns/nk) sum_Q conj(V[0][k'][Q][b][a]) vbar[Q]
-  g = gemm_desc();
+  GemmDesc g = gemm_desc();
   g.A = vb; g.B = Vd; g.C = gb;
   g.M = 1; g.N = nk * (int)n2; g.K = naux;
   g.am = aff(0); g.ak = aff(1);
@@ -1865,32 +1897,9 @@ gw_status gw_hf_vjp(gw_ctx* c, const void* V, const gw_z* Sbar, gw_z* Gbar) {
   g.tb = tv;
   g.tag = KC_HF;
   if ((s = run(c, g, Ext{0, (long long)naux}, Ext{0, (long long)nk * sv}, Ext{0, (long long)nk * n2})) != GW_OK) return s;
-  for (int q = 0; q < nk; ++q) {
-    const char* Aq = Vd + (size_t)q * nk * sv * ez;
-    // T2[k][Q][b][i] = sum_j V[q][k][Q][j][b] Sbar[k][i][j]
-    g = gemm_desc();
-    g.A = Aq; g.B = Sbar; g.C = T2;
-    g.M = naux * nao; g.N = nao; g.K = nao; g.batch = nk;
-    g.am = two(nao, 1, n2); g.ak = aff(nao); g.bk = aff(1); g.bn = aff(nao);
-    g.cm = aff(nao); g.cn = aff(1);
-    g.ba = aff(sv); g.bb = aff(n2); g.bc = aff(sv);
-    g.ta = tv;
-    g.tag = KC_HF;
-    if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)nk * n2}, Ext{0, (long long)nk * sv})) != GW_OK) return s;
-    // gbar[k+q][a][b] += -(1/nk) sum_{Q,i} conj(V[q][k][Q][i][a]) T2[k][Q][b][i]
-    g = gemm_desc();
-    g.A = Aq; g.B = T2; g.C = gb;
-    g.M = nao; g.N = nao; g.K = naux * nao; g.batch = nk;
-    g.am = aff(1); g.ak = two(nao, nao, n2); g.conjA = 1;
-    g.bk = two(nao, 1, n2); g.bn = aff(nao);
-    g.cm = aff(nao); g.cn = aff(1);
-    g.ba = aff(sv); g.bb = aff(sv); g.bc = aff(0);
-    g.tab = c->dplus + (size_t)q * nk; g.tmod = nk; g.tsC = n2;
-    g.alpha_r = -1.0 / nk; g.beta_zero = 0; g.beta_r = 1.0;
-    g.ta = tv;
-    g.tag = KC_HF;
-    if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)nk * sv}, Ext{0, (long long)nk * n2})) != GW_OK) return s;
-  }
+  // gbar[k+q] += -(1/nk) sum_Q V[q][k][Q]^H Sbar[k] V[q][k][Q]: the adjoint of
+  // X -> V X V^H; the targets of two q overlap, so one q after the other
+  if ((s = exchange(c, Vd, (const double2*)Sbar, T2, gb, false)) != GW_OK) return s;
   // Gbar[t] += -w_t gbar   (gamma = -sum_t w_t G(t), w real)
   g = gemm_desc();
   g.A = c->dw; g.B = gb; g.C = Gbar;
@@ -2202,9 +2211,13 @@ gw_status gw_sigma_jvp(gw_ctx* c, const void* V, const gw_z* G, const gw_z* Pt_t
       const char *Vd = (const char*)V, *Gd = (const char*)G, *dGd = (const char*)dG;
       const bool self = c->neg[q] == q;
       const int te = self ? nt / 2 : nt;
-      if ((s = pol_nodes(c, ctx_work(c), Vd, dGd, Gd, q, 0, te, p.tb, false, true)) != GW_OK) return s;
-      if ((s = pol_nodes(c, ctx_work(c), Vd, Gd, dGd, q, 0, te, p.tb, true, true)) != GW_OK) return s;
+      if ((s = pol_nodes(c, ctx_work(c), Vd, dGd, Gd, q, 0, te, p.tb, false, true, Gd, dGd)) != GW_OK) return s;
       if ((s = pol_finish(c, p.tb, self ? p.tb : nullptr, 0, te, true)) != GW_OK) return s;
+    } else if (!lowp(c)) {
+      const bool herm = (c->herm & GW_HERM_TWO_SLOT) != 0;
+      if ((s = pol_nodes(c, ctx_work(c), (const char*)V, (const char*)dG, (const char*)G, q, 0, nt, p.tb, false, herm,
+                         (const char*)G, (const char*)dG)) != GW_OK) return s;
+      if ((s = pol_finish(c, p.tb, nullptr, 0, nt, herm)) != GW_OK) return s;
     } else {
       if ((s = pol_impl(c, ctx_work(c), V, dG, G, q, 1, p.tb, false, true)) != GW_OK) return s;
       if ((s = pol_impl(c, ctx_work(c), V, G, dG, q, 1, p.tb, true, true)) != GW_OK) return s;

@@ -144,6 +144,49 @@ struct DysonArgs {
   double* logdet;        // may be null: logdet[n*nk+k] = ln|det M| of the Dyson matrix
 };
 
+// Y[t][k][Q] = L V[k][Q] R for t < nt, k < nk, Q < naux (nao x nao matrices,
+// complex128).  L and R are the matrices L + t tsL + k' nao^2 and
+// R + t tsR + k' nao^2 with k' = k, or tab[k] where tabL / tabR is set; hermL
+// takes L^H.  V and Y have k stride svk and Q stride nao^2, Y the t stride
+// tsY.  accumulate adds to Y.
+struct SandProd {
+  const double2 *V, *L, *R;
+  double2* Y;
+  const int* tab;
+  int nt, nk, naux, nao;
+  long long svk, tsL, tsR, tsY;
+  int tabL, tabR, hermL, accumulate;
+  int qlen;           // filled by the launcher: Q per workgroup
+};
+
+// O[t][k'] (+)= alpha sum_Q A^H G B (bh = 0) or A G B^H (bh = 1) for t < nt,
+// k < nk, with A = A + t tsA + k skA + Q sqA (complex128, or complex64 with
+// tv = 1) and B likewise; G + t tsG + k' nao^2 and O + t tsO + k' nao^2 with
+// k' = k, or tab[t tstab + k] where tabG / tabO is set; hermG takes G^H.
+// Strides count elements.  part (part_elems numbers, may be null) lets the
+// launcher split Q; fold_t (needs part) also sums over t, into O + k' nao^2.
+struct SandSum {
+  const void *A, *B;
+  const double2* G;
+  double2* O;
+  const int* tab;
+  int nt, nk, naux, nao;
+  long long tsA, skA, sqA, tsB, skB, sqB, tsG, tsO, tstab;
+  int tabG, tabO, hermG, bh, tv, accumulate;
+  double alpha;
+  double2* part;
+  long long part_elems;
+  int fold_t;
+  int qlen;           // filled by the launcher: Q per workgroup
+};
+
+hipError_t sand_prod_launch(const SandProd& d, hipStream_t st);
+hipError_t sand_sum_launch(const SandSum& d, hipStream_t st);
+// out[Q] = alpha sum_{k,e} V[k][Q][e] X[k][e] for Q < naux (V conjugated with
+// conj; X[k] transposed with transpose; V complex64 with tv = 1)
+hipError_t vdot_launch(const void* V, int tv, const double2* X, double2* out, int nk, int naux, int nao, double alpha,
+                       bool conj, bool transpose, hipStream_t st);
+
 hipError_t zgemm_launch(const GemmDesc& d, hipStream_t st);
 // true when zgemm_launch runs d on the three-product (Gauss) form: 6 real
 // MFMA flops per complex multiply-add instead of 8
