@@ -968,15 +968,15 @@ static gw_status pol_split_chunk(gw_ctx* c, const char* Aq, const char* Gd, cons
   return GW_OK;
 }
 
-// The tau nodes [tb, te) of P0^q, written to P0, the
-// [ntau][naux][naux] array of this q; Gd and Gbd are the two G slots in
-// the chain's storage type.  With herm only the output tiles on and above the
-// diagonal are valid afterwards (pol_finish fills the rest).  fp64: Gd2 and
-// Gbd2 (may be NULL) are a second pair of slots, added to the first one's
-// term before the long contraction.
+// The tau nodes [tb, te) of P0^q, written to P0, the [ntau][naux][naux] array
+// of this q, and with M0 the mirrored nodes M0[ntau-1-i] = P0[i]^T of -q; Gd
+// and Gbd are the two G slots in the chain's storage type.  herm: P0 is
+// Hermitian, and only its upper half is contracted.  fp64: Gd2 and Gbd2 (may
+// be NULL) are a second pair of slots, added to the first one's term before
+// the long contraction.
 static gw_status pol_nodes(gw_ctx* c, const Work& w, const char* Vd, const char* Gd, const char* Gbd, int q,
-                           int tb, int te, gw_z* P0, bool accumulate, bool herm, const char* Gd2 = nullptr,
-                           const char* Gbd2 = nullptr);
+                           int tb, int te, gw_z* P0, gw_z* M0, bool accumulate, bool herm,
+                           const char* Gd2 = nullptr, const char* Gbd2 = nullptr);
 
 // Completes the nodes [tb, te) of one q: the lower triangle in Hermitian
 // mode, and with M0 the mirrored nodes M0[ntau-1-i] = P0[i]^T of -q.
@@ -1036,15 +1036,15 @@ static gw_status pol_impl(gw_ctx* c, const Work& w, const void* V, const gw_z* G
     if (has && m < q) continue;
     const int te = has && m == q ? nt / 2 : nt;
     gw_z* Pq = P0 + (q - q0) * per;
-    gw_status s = pol_nodes(c, w, (const char*)V, Gd, Gbd, q, 0, te, Pq, accumulate, herm);
+    gw_status s = pol_nodes(c, w, (const char*)V, Gd, Gbd, q, 0, te, Pq, has ? P0 + (m - q0) * per : nullptr,
+                            accumulate, herm);
     if (s != GW_OK) return s;
-    if ((s = pol_finish(c, Pq, has ? P0 + (m - q0) * per : nullptr, 0, te, herm)) != GW_OK) return s;
   }
   return GW_OK;
 }
 
 static gw_status pol_nodes(gw_ctx* c, const Work& w, const char* Vd, const char* Gd, const char* Gbd, int q,
-                           int tb, int te, gw_z* P0, bool accumulate, bool herm, const char* Gd2,
+                           int tb, int te, gw_z* P0, gw_z* M0, bool accumulate, bool herm, const char* Gd2,
                            const char* Gbd2) {
   const int tc = w.tc;
   const int nk = c->nk, nao = c->d.nao, naux = c->d.naux, nt = c->d.ntau;
@@ -1083,6 +1083,25 @@ static gw_status pol_nodes(gw_ctx* c, const Work& w, const char* Vd, const char*
         p.accumulate = 1;
         if ((s = sand_prod(c, p, KC_POL_PRODUCER)) != GW_OK) return s;
       }
+      const long long nn = (long long)naux * naux, room = (long long)tc * S;
+      if (n2 >= 4 && c->tile_cfg < 0 && room >= tcur * pol_acc_blocks(naux, herm) * 256) {
+        PolAcc a{};
+        a.Y = (const double2*)X; a.V = (const double2*)Aq;
+        a.P = (double2*)P0 + t0 * nn;
+        a.M = M0 ? (double2*)M0 + (nt - 1 - t0) * nn : nullptr;
+        a.part = (double2*)Z;
+        a.nt = tcur; a.naux = naux; a.n2 = (int)n2; a.K = nk * (int)n2;
+        a.tsY = S; a.sv = sv; a.tri = herm; a.accumulate = accumulate;
+        a.alpha = -(double)c->d.ns / nk;
+        hipEvent_t e0 = nullptr;
+        if ((s = prof_begin(c, KC_POL_CONTRACT, &e0)) != GW_OK) return s;
+        HIPCHK(c, pol_acc_launch(a, room, c->st));
+        const double outs = herm ? 0.5 * naux * (naux + 1.0) : (double)nn;
+        if ((s = prof_end(c, KC_POL_CONTRACT, e0, 6.0 * outs * a.K * tcur)) != GW_OK) return s;
+        continue;
+      }
+      // matrices of one orbital, a chunk without room for the partial sums, or
+      // a tile configuration asked for
       GemmDesc g = gemm_desc();
       g.A = X; g.B = Aq; g.C = (double2*)P0 + (long long)t0 * naux * naux;
       g.M = naux; g.N = naux; g.K = nk * (int)n2; g.batch = tcur;
@@ -1096,6 +1115,7 @@ static gw_status pol_nodes(gw_ctx* c, const Work& w, const char* Vd, const char*
       g.tag = KC_POL_CONTRACT;
       if ((s = run(c, g, Ext{0, (long long)tcur * S}, Ext{0, S}, Ext{0, (long long)tcur * naux * naux})) != GW_OK)
         return s;
+      if ((s = pol_finish(c, P0, M0, t0, t0 + tcur, herm)) != GW_OK) return s;
       continue;
     }
     // X[tl][k][Q][d][b] = sum_a V[q][k][Q][d][a] G[t0+tl][k+q][a][b]
@@ -1142,7 +1162,7 @@ static gw_status pol_nodes(gw_ctx* c, const Work& w, const char* Vd, const char*
     g.tri = herm ? 1 : 0;
     if ((s = run(c, g, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * naux * naux})) != GW_OK) return s;
   }
-  return GW_OK;
+  return f32 ? pol_finish(c, P0, M0, tb, te, herm) : GW_OK;
 }
 
 // ------------------------------------------------------------- transforms
@@ -2161,8 +2181,7 @@ gw_status gw_sigma(gw_ctx* c, const void* V, const gw_z* G, gw_z* gamma, gw_z* S
       }
       // P0^{-q} by transposition, then one q after the other
       if ((s = pol_nodes(c, ctx_work(c), (const char*)V, (const char*)G, (const char*)G, q, 0, c->d.ntau, p.ta,
-                         false, herm)) != GW_OK) return s;
-      if ((s = pol_finish(c, p.ta, p.tb, 0, c->d.ntau, herm)) != GW_OK) return s;
+                         p.tb, false, herm)) != GW_OK) return s;
       if ((s = pt_solve(c, p.ta, p, phi ? &ph : nullptr)) != GW_OK) return s;
       if ((s = gw_self_energy(c, V, G, p.ta, q, 1, Stau)) != GW_OK) return s;
       if ((s = pt_solve(c, p.tb, p, phi ? &ph : nullptr)) != GW_OK) return s;
@@ -2211,13 +2230,12 @@ gw_status gw_sigma_jvp(gw_ctx* c, const void* V, const gw_z* G, const gw_z* Pt_t
       const char *Vd = (const char*)V, *Gd = (const char*)G, *dGd = (const char*)dG;
       const bool self = c->neg[q] == q;
       const int te = self ? nt / 2 : nt;
-      if ((s = pol_nodes(c, ctx_work(c), Vd, dGd, Gd, q, 0, te, p.tb, false, true, Gd, dGd)) != GW_OK) return s;
-      if ((s = pol_finish(c, p.tb, self ? p.tb : nullptr, 0, te, true)) != GW_OK) return s;
+      if ((s = pol_nodes(c, ctx_work(c), Vd, dGd, Gd, q, 0, te, p.tb, self ? p.tb : nullptr, false,
+                         true, Gd, dGd)) != GW_OK) return s;
     } else if (!lowp(c)) {
       const bool herm = (c->herm & GW_HERM_TWO_SLOT) != 0;
-      if ((s = pol_nodes(c, ctx_work(c), (const char*)V, (const char*)dG, (const char*)G, q, 0, nt, p.tb, false, herm,
-                         (const char*)G, (const char*)dG)) != GW_OK) return s;
-      if ((s = pol_finish(c, p.tb, nullptr, 0, nt, herm)) != GW_OK) return s;
+      if ((s = pol_nodes(c, ctx_work(c), (const char*)V, (const char*)dG, (const char*)G, q, 0, nt, p.tb,
+                         nullptr, false, herm, (const char*)G, (const char*)dG)) != GW_OK) return s;
     } else {
       if ((s = pol_impl(c, ctx_work(c), V, dG, G, q, 1, p.tb, false, true)) != GW_OK) return s;
       if ((s = pol_impl(c, ctx_work(c), V, G, dG, q, 1, p.tb, true, true)) != GW_OK) return s;

@@ -180,6 +180,27 @@ struct SandSum {
   int qlen;           // filled by the launcher: Q per workgroup
 };
 
+// P[t][Q][Q'] = alpha sum_{k<nk, e<n2} Y[t][k][Q][e] conj(V[k][Q'][e]) for
+// t < nt, K = nk n2; k stride sv and Q stride n2 of V and Y, t stride tsY of Y.
+// tri: only the blocks on and above the diagonal are contracted, the others
+// become their conjugates.  accumulate adds to P (with tri: to its upper
+// triangle).  M (may be null): M[-t] = the transpose of P[t].  part holds the
+// sums of the K parts (pol_acc_launch: part_elems numbers, at least
+// nt * 256 * pol_acc_blocks).  Needs n2 >= 4.
+struct PolAcc {
+  const double2 *Y, *V;
+  double2 *P, *M, *part;
+  int nt, naux, n2, K;
+  long long tsY, sv;
+  int tri, accumulate;
+  double alpha;
+  // filled by the launcher: block rows, superblocks per side, blocks, parts,
+  // blocks per part, K parts and their steps of 8
+  int nb, ns, nblk, nparts, per, nsplit, steps;
+};
+
+long long pol_acc_blocks(int naux, bool tri);
+hipError_t pol_acc_launch(const PolAcc& d, long long part_elems, hipStream_t st);
 hipError_t sand_prod_launch(const SandProd& d, hipStream_t st);
 hipError_t sand_sum_launch(const SandSum& d, hipStream_t st);
 // out[Q] = alpha sum_{k,e} V[k][Q][e] X[k][e] for Q < naux (V conjugated with

@@ -10,11 +10,19 @@
 // dealt to the waves up to 7 each (3 accumulator sets of 7 blocks are 168
 // VGPRs: two waves per SIMD), so that a triangle wastes only the lower halves
 // of its diagonal blocks (64 x 64 tiles of naux 150 execute 2.2 times the
-// triangle, the blocks 1.24 times).  The rows of Y and V that a workgroup's
-// blocks need go through two LDS stages of 4 k as operand fragments (lane
-// order, no bank conflicts): each is read from L2 once per workgroup, and the
-// loads of the next stage have a whole stage of MFMAs (7 x 3 x 64 cycles times
-// two waves per SIMD) to arrive.
+// triangle, the blocks 1.24 times).  fp64 MFMAs and vector instructions share
+// the SIMD's fp64 pipe here (measured: each v_xor_b32 between 16x16x4 MFMAs
+// costs 5 cycles, each v_add_f64 10, of 64 per MFMA), so the loop keeps the
+// latter out: the rows of Y and V that a workgroup's blocks need go through
+// LDS as operand fragments with their sums re +- im formed once per workgroup,
+// and addresses are per-stage increments or scalars.  Two LDS stages of 8 k:
+// each row is read from L2 in whole lines once per workgroup, and loads have a
+// whole stage of MFMAs (2 x 7 x 3 x 64 cycles times two waves per SIMD) to
+// arrive; half of the waves change stages in each half of a stage, so that the
+// two waves of a SIMD rarely leave its pipe together.  Measured for one q (ms,
+// 64 x 64 tiles of zgemm_k with four products before): 18.0 vs 22.5 at 4x4x4,
+// nao 26, naux 250, 100 nodes (0.70 of the MFMA peak executed); 0.69 vs 1.76 at
+// 3x3x3, nao 16, naux 150, 60 nodes.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -25,7 +33,7 @@
 namespace {
 
 constexpr int kMaxBlk = 7;      // blocks of a wave
-constexpr int kPartBlk = 28;    // blocks of a workgroup (4 waves)
+constexpr int kPartBlk = 56;    // blocks of the largest workgroup (8 waves)
 constexpr int kSuper = 16;      // largest side of a superblock
 
 // A part: up to kPartBlk consecutive blocks (row by row) of one superblock pair.
@@ -87,13 +95,22 @@ struct Acc3 {
   d4 p1, p2, p3;
 };
 
+// One element of a fragment in LDS; the 24-byte lane stride visits every bank
+// once per 32 lanes.
+struct Elem {
+  double r, i, s;
+};
+
 }  // namespace
 
-// W waves, each loading L fragments per stage; a workgroup's blocks touch at
-// most W * L fragment rows (checked by the launcher).
-template <int W, int L>
+// W waves of M blocks each, loading L fragment rows per stage; a workgroup's
+// blocks touch at most W * L fragment rows.  A wave past the last block
+// repeats it, so that the loop has no branches.  AL: n2 is a multiple of 4, so
+// the four k of a fragment never straddle two k-points and the K offset is a
+// scalar.
+template <int W, int L, int M, bool AL>
 __global__ void __launch_bounds__(64 * W) pol_acc_k(PolAcc d) {
-  __shared__ double2 lds[2][W * L * 64];
+  __shared__ Elem lds[4 * W * L * 64];
   const int lane = threadIdx.x & 63, r16 = lane & 15, kl = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // contiguous logical ids per XCD (ids are dealt round-robin over the 8):
@@ -117,91 +134,151 @@ __global__ void __launch_bounds__(64 * W) pol_acc_k(PolAcc d) {
   }
   const int nf = na + cz - ca + 1;
 
-  const int nsteps_all = (d.K + 3) / 4;
-  const int s0 = sp * d.steps, s1 = min(s0 + d.steps, nsteps_all);
-  // this lane's fragment elements: row pointers and the running K offset
+  const int s0 = sp * d.steps, s1 = min(s0 + d.steps, (d.K + 7) / 8);
+  // fragment rows of this wave: matrix, byte offset of this lane's row, place
+  // in a stage and sign of the sum (rows past the last repeat it: the same
+  // values to the same place)
   const double2* src[L];
-  bool has[L];
+  unsigned vo[L];
+  double sg[L];
+  int at[L];
 #pragma unroll
   for (int l = 0; l < L; ++l) {
-    const int f = wave + W * l;
-    has[l] = f < nf;
+    const int f = min(wave + W * l, nf - 1);
     const bool y = f < na;
     const int row = 16 * (y ? p.r0 + ra + f : p.c0 + ca + (f - na)) + r16;
-    src[l] = (y ? d.Y + t * d.tsY : d.V) + (long long)min(row, d.naux - 1) * d.n2;
+    src[l] = y ? d.Y + t * d.tsY : d.V;
+    sg[l] = y ? 1.0 : -1.0;               // B = conj(V)
+    vo[l] = ((unsigned)min(row, d.naux - 1) * (unsigned)d.n2 + (unsigned)kl) * 16u;
+    at[l] = (f * 64 + lane) * (int)sizeof(Elem);
   }
-  int e = 0;
-  long long koff = 0;
-  int kk = 4 * s0 + kl;             // k of the next stage to load
-  {
-    const int k = kk / d.n2;
-    e = kk - k * d.n2;
-    koff = (long long)k * d.sv + e;
-  }
-  double2 f[L];
-  bool ok = true;
+  // k = ku n2 + e0 starts the stage to load
+  const int n2 = d.n2, nk = d.K / n2;
+  int k0 = 8 * s0, ku = k0 / n2, e0 = k0 - ku * n2;
+  double2 f[2][L];
   auto fetch = [&]() {
-    // lanes past K read k = 0 of their row and store zeros
-    ok = kk < d.K;
-    const long long o = ok ? koff : 0;
 #pragma unroll
-    for (int l = 0; l < L; ++l)
-      if (has[l]) f[l] = src[l][o];
-    kk += 4;
-    e += 4;
-    koff += 4;
-    if (e >= d.n2) {                // n2 >= 4: one carry
-      e -= d.n2;
-      koff += d.sv - d.n2;
+    for (int h = 0; h < 2; ++h) {
+      // k past K reads its row's first elements (stash stores zeros)
+      if constexpr (AL) {
+        const long long kb = k0 + 4 * h < d.K ? ku * d.sv + e0 : 0;
+#pragma unroll
+        for (int l = 0; l < L; ++l) f[h][l] = *(const double2*)((const char*)(src[l] + kb) + vo[l]);
+        e0 += 4;
+        if (e0 >= n2) {
+          e0 -= n2;
+          ++ku;
+        }
+      } else {
+        const long long kb = min(ku, nk - 1) * d.sv;
+        unsigned e = (unsigned)(e0 + kl), c = 0;
+        if (e >= (unsigned)n2) {
+          e -= n2;
+          c = (unsigned)d.sv;
+        }
+        if (k0 + 4 * h + kl >= d.K) e = c = 0;
+        const unsigned eo = (e + c - (unsigned)kl) * 16u;
+#pragma unroll
+        for (int l = 0; l < L; ++l) f[h][l] = *(const double2*)((const char*)(src[l] + kb) + (unsigned long long)(vo[l] + eo));
+        e0 += 4;
+        if (e0 >= n2) {                    // n2 >= 4: one carry
+          e0 -= n2;
+          ++ku;
+        }
+      }
     }
+    k0 += 8;
   };
-  auto stash = [&](int stage) {
+  // into the stage at byte offset `stage`; kk: its first k
+  char* const lb = (char*)lds;
+  constexpr int kHalf = W * L * 64 * (int)sizeof(Elem), kStage = 2 * kHalf;
+  auto stash = [&](int stage, int kk) {
+    if (!AL && kk + 8 > d.K) {
 #pragma unroll
-    for (int l = 0; l < L; ++l)
-      if (has[l]) lds[stage][(wave + W * l) * 64 + lane] = ok ? f[l] : double2{0.0, 0.0};
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int l = 0; l < L; ++l)
+          if (kk + 4 * h + kl >= d.K) f[h][l] = double2{0.0, 0.0};
+    }
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      char* q = lb + stage + at[l];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const double2 v = f[h][l];
+        *(Elem*)(q + h * kHalf) = Elem{v.x, v.y, __builtin_fma(sg[l], v.y, v.x)};
+      }
+    }
   };
 
   // this wave's blocks
   const int m = (p.cnt + W - 1) / W;
   const int mine = min(m, p.cnt - wave * m);   // may be <= 0
-  int fa[kMaxBlk], fb[kMaxBlk];
+  int fa[M], fb[M];                            // byte offsets of their fragments in the current stage
 #pragma unroll
-  for (int b = 0; b < kMaxBlk; ++b) {
-    block_rc(p.cols, p.diag, p.b0 + min(wave * m + b, p.cnt - 1), rt, ct);
-    fa[b] = (rt - ra) * 64 + lane;
-    fb[b] = (na + ct - ca) * 64 + lane;
+  for (int b = 0; b < M; ++b) {
+    block_rc(p.cols, p.diag, p.b0 + min(wave * m + min(b, m - 1), p.cnt - 1), rt, ct);
+    fa[b] = ((rt - ra) * 64 + lane) * (int)sizeof(Elem);
+    fb[b] = ((na + ct - ca) * 64 + lane) * (int)sizeof(Elem);
   }
-  Acc3 o[kMaxBlk];
+  Acc3 o[M];
 #pragma unroll
-  for (int b = 0; b < kMaxBlk; ++b) o[b].p1 = o[b].p2 = o[b].p3 = d4{0, 0, 0, 0};
+  for (int b = 0; b < M; ++b) o[b].p1 = o[b].p2 = o[b].p3 = d4{0, 0, 0, 0};
 
   if (s0 < s1) {
     fetch();
-    stash(0);
+    stash(0, 8 * s0);
+    fetch();
     __syncthreads();
+    int flip = kStage;
+    const bool late = wave >= W / 2;
+    // The next stage moves from registers to LDS, and the one after it starts
+    // to load, in the middle of the MFMAs, half of the waves in each half of
+    // the stage: the two waves of a SIMD then rarely leave the pipe together.
+    // No branch around single loads (each would wait for the one before); the
+    // last ones go unused.
+    auto turn = [&](int s) {
+      stash(flip > 0 ? kStage : 0, 8 * s + 8);
+      fetch();
+      __builtin_amdgcn_sched_barrier(0);
+    };
     for (int s = s0; s < s1; ++s) {
-      const int st = (s - s0) & 1;
-      if (s + 1 < s1) fetch();
-      __builtin_amdgcn_sched_barrier(0);   // the loads first, then the MFMAs they hide behind
 #pragma unroll
-      for (int b = 0; b < kMaxBlk; ++b)
-        if (b < mine) {
-          const double2 x = lds[st][fa[b]], v = lds[st][fb[b]];
-          o[b].p1 = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, v.x, o[b].p1, 0, 0, 0);
-          o[b].p2 = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, -v.y, o[b].p2, 0, 0, 0);
-          o[b].p3 = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x + x.y, v.x - v.y, o[b].p3, 0, 0, 0);
+      for (int h = 0; h < 2; ++h) {
+        if (AL && h == 1 && 8 * s + 4 >= d.K) break;   // K is a multiple of 4, this half is past it
+        Elem x[2], v[2];
+        x[0] = *(const Elem*)(lb + fa[0] + h * kHalf);
+        v[0] = *(const Elem*)(lb + fb[0] + h * kHalf);
+#pragma unroll
+        for (int b = 0; b < M; ++b) {
+          if (b + 1 < M) {                 // the next block's elements
+            x[(b + 1) & 1] = *(const Elem*)(lb + fa[b + 1] + h * kHalf);
+            v[(b + 1) & 1] = *(const Elem*)(lb + fb[b + 1] + h * kHalf);
+          }
+          o[b].p1 = __builtin_amdgcn_mfma_f64_16x16x4f64(x[b & 1].r, v[b & 1].r, o[b].p1, 0, 0, 0);
+          o[b].p2 = __builtin_amdgcn_mfma_f64_16x16x4f64(x[b & 1].i, v[b & 1].i, o[b].p2, 0, 0, 0);
+          o[b].p3 = __builtin_amdgcn_mfma_f64_16x16x4f64(x[b & 1].s, v[b & 1].s, o[b].p3, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);   // keeps the live elements at two blocks
+          if (b == M / 2 && late == (h == 1)) turn(s);
         }
-      if (s + 1 < s1) stash(st ^ 1);
+      }
+#pragma unroll
+      for (int b = 0; b < M; ++b) {
+        fa[b] += flip;
+        fb[b] += flip;
+      }
+      flip = -flip;
       __syncthreads();
     }
   }
+  // with V unconjugated in p2: re = p1 + p2, im = p3 - p1 + p2
   double2* out = d.part + (((long long)sp * d.nt + t) * d.nblk + p.g0 + wave * m) * 256 + lane;
 #pragma unroll
-  for (int b = 0; b < kMaxBlk; ++b)
+  for (int b = 0; b < M; ++b)
     if (b < mine) {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        out[b * 256 + q * 64] = double2{o[b].p1[q] - o[b].p2[q], o[b].p3[q] - o[b].p1[q] - o[b].p2[q]};
+        out[b * 256 + q * 64] = double2{o[b].p1[q] + o[b].p2[q], o[b].p3[q] - o[b].p1[q] + o[b].p2[q]};
     }
 }
 
@@ -291,23 +368,28 @@ hipError_t pol_acc_launch(const PolAcc& d0, long long part_elems, hipStream_t st
   d.ns = pol_supers(d.nb);
   d.nblk = (int)pol_acc_blocks(d.naux, d.tri != 0);
   if (part_elems < (long long)d.nt * d.nblk * 256) return hipErrorInvalidValue;
-  // one wave up to 7 blocks, two up to 14, otherwise four per workgroup
-  const int W = d.nblk <= kMaxBlk ? 1 : d.nblk <= 2 * kMaxBlk ? 2 : 4;
-  d.per = W == 4 ? kPartBlk : kMaxBlk * W;
+  // one wave up to 6 blocks, two up to 12, four up to 24 (12 fragment rows:
+  // 74 KB of LDS, two workgroups per CU), otherwise eight and as many parts as
+  // keep a wave at 7 blocks
+  const int W = d.nblk <= 6 ? 1 : d.nblk <= 12 ? 2 : d.nblk <= 24 ? 4 : 8;
+  d.per = W == 8 ? kPartBlk : 6 * W;
   d.nparts = 0;
+  int M = 1;                       // blocks of a wave
   each_pair(d.nb, d.ns, d.tri != 0, [&](int, int, int rows, int cols, bool diag) {
-    d.nparts += (pair_blocks(rows, cols, diag) + d.per - 1) / d.per;
+    const int n = pair_blocks(rows, cols, diag), np = (n + d.per - 1) / d.per;
+    d.nparts += np;
+    M = std::max(M, ((n + np - 1) / np + W - 1) / W);
     return false;
   });
   // K parts: two waves per SIMD run at once; the count that ends its rounds
-  // of workgroups soonest (a part costs about 24 steps of start and end)
-  const long long slots = 256 * (8 / W), wgs = (long long)d.nparts * d.nt;
-  const int steps = (d.K + 3) / 4;
+  // of workgroups soonest (a part costs about 12 steps of start and end)
+  const long long slots = W == 8 ? 256 : W == 1 ? 1024 : 512, wgs = (long long)d.nparts * d.nt;
+  const int steps = (d.K + 7) / 8;
   const long long room = part_elems / ((long long)d.nt * d.nblk * 256);
   int best = 1;
   double cost = 0.0;
   for (int s = 1; s <= 64 && s <= room && s <= steps; ++s) {
-    const double c = (double)((wgs * s + slots - 1) / slots) * ((steps + s - 1) / s + 24);
+    const double c = (double)((wgs * s + slots - 1) / slots) * ((steps + s - 1) / s + 12);
     if (s == 1 || c < cost) {
       best = s;
       cost = c;
@@ -317,9 +399,27 @@ hipError_t pol_acc_launch(const PolAcc& d0, long long part_elems, hipStream_t st
   d.nsplit = (steps + d.steps - 1) / d.steps;
   if (wgs * d.nsplit > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)(wgs * d.nsplit));
-  if (W == 1) pol_acc_k<1, 6><<<grid, 64, 0, st>>>(d);
-  else if (W == 2) pol_acc_k<2, 4><<<grid, 128, 0, st>>>(d);
-  else pol_acc_k<4, 5><<<grid, 256, 0, st>>>(d);
+#define POL_CALL(W_, L_, M_)                                                    \
+  do {                                                                          \
+    if (d.n2 % 4 == 0) pol_acc_k<W_, L_, M_, true><<<grid, 64 * W_, 0, st>>>(d); \
+    else pol_acc_k<W_, L_, M_, false><<<grid, 64 * W_, 0, st>>>(d);             \
+  } while (0)
+  if (W == 8) {
+    if (M == 7) POL_CALL(8, 3, 7);
+    else if (M == 6) POL_CALL(8, 3, 6);
+    else if (M == 5) POL_CALL(8, 3, 5);
+    else POL_CALL(8, 3, 4);
+  } else if (W == 4) {
+    if (M == 6) POL_CALL(4, 3, 6);
+    else POL_CALL(4, 3, 4);
+  } else if (W == 2) {
+    POL_CALL(2, 4, 5);
+  } else {
+    if (M == 1) POL_CALL(1, 2, 1);
+    else if (M <= 4) POL_CALL(1, 4, 4);
+    else POL_CALL(1, 6, 6);
+  }
+#undef POL_CALL
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   pol_fin_k<<<dim3((unsigned)d.nblk, (unsigned)d.nt), 256, 0, st>>>(d);
