@@ -10,14 +10,15 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgw.so")
-SOURCES = ["gw_kernels.hip", "gw_sandwich.hip", "gw_polar.hip", "gw_api.hip", "grids.cpp", "ir.cpp"]
+SOURCES = ["gw_kernels.hip", "gw_sandwich.hip", "gw_polar.hip", "gw_dyson.hip", "gw_api.hip", "grids.cpp", "ir.cpp"]
 
 
 def source_hash():
     """sha256 of the kernel and ABI sources (names counter summaries to a build)."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("gw_kernels.hip", "gw_sandwich.hip", "gw_polar.hip", "gw_kernels.h", "gw_device.h", "gw_api.hip"):
+    for f in ("gw_kernels.hip", "gw_sandwich.hip", "gw_polar.hip", "gw_dyson.hip",
+              "gw_kernels.h", "gw_device.h", "gw_api.hip"):
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

@@ -142,6 +142,7 @@ struct DysonArgs {
   double* part;          // may be null
   int* flag;
   double* logdet;        // may be null: logdet[n*nk+k] = ln|det M| of the Dyson matrix
+  double more[15];       // dyson_reg_launch: further mu values
 };
 
 // Y[t][k][Q] = L V[k][Q] R for t < nt, k < nk, Q < naux (nao x nao matrices,
@@ -214,6 +215,12 @@ hipError_t zgemm_launch(const GemmDesc& d, hipStream_t st);
 bool zgemm_three_product(const GemmDesc& d);
 hipError_t bsgemm_launch(const SplitDesc& d, hipStream_t st);
 hipError_t dyson_launch(const DysonArgs& a, int nw, hipStream_t st);
+// The same for nao <= 32, one wave per matrix; nmu values of mu (a.mu, then
+// a.more) with part[(i * nw + n) * nk + k]; G and logdet of the first one only
+// (nmu = 1).
+hipError_t dyson_reg_launch(const DysonArgs& a, int nw, int nmu, hipStream_t st);
+// out[b] = scale * (x[b n] + ... + x[b n + n - 1]) for b < rows
+hipError_t sum_rows_launch(const double* x, int n, int rows, double scale, double* out, hipStream_t st);
 hipError_t sum_launch(const double* x, long long n, double scale, double* out, hipStream_t st);
 hipError_t trace_launch(const double2* g, const double2* S, int n, int nk, double* part,
                         hipStream_t st);
