@@ -241,6 +241,11 @@ hipError_t wtrace_launch(const double2* P, const double2* S, const double2* r, i
 // transpose of the (completed) matrix.
 hipError_t mirror_launch(double2* src, double2* dst, long long dstep, int n, long long nmat, bool herm,
                          hipStream_t st);
+// X(-Omega) = X(Omega)^H and, for the partner -q, X^{-q}(Omega) = conj(X^q(Omega))
+// written from the matrices at Omega >= 0: for i < nq and mid <= m < nw the
+// matrix at X + (q nw + m) n^2, q = reps[i] (0 if reps is null), fills (q, nw-1-m)
+// and, where negs[i] != q, (negs[i], m) and (negs[i], nw-1-m).
+hipError_t spread_launch(double2* X, const int* reps, const int* negs, int nq, int nw, int mid, int n, hipStream_t st);
 // P[b] <- (P[b] + P[b]^H) / 2 for b < nmat (n x n, row-major).
 hipError_t herm_avg_launch(double2* P, int n, long long nmat, hipStream_t st);
 // Eq. tilde_Phi_GW: for each of nmat matrices m of an LU-factorised I - P0
@@ -253,5 +258,8 @@ hipError_t phi_terms_launch(const double2* LU, const double2* P0, int n, long lo
 // b < nmat (nk S matrices, nmat X and Out matrices, all n x n, n <= 64).
 hipError_t sxs_add_launch(const double2* S, const double2* X, double2* Out, int n, int nk,
                           long long nmat, double alpha, hipStream_t st);
-hipError_t wlu_launch(int which, const double2* P0, double2* A, double2* B, int n, int j0, int nb,
+// Pieces of the blocked LU solve of (I - P0) X = P0 for nmat n x n matrices:
+// A holds them one after the other, P0 and B (the solution) have matrix b at
+// position sel[b] (b if sel is null).
+hipError_t wlu_launch(int which, const double2* P0, double2* A, double2* B, const int* sel, int n, int j0, int nb,
                       long long nmat, int* flag, hipStream_t st);

@@ -1401,6 +1401,48 @@ hipError_t mirror_launch(double2* src, double2* dst, long long dstep, int n, lon
   return hipGetLastError();
 }
 
+// Fills X at negative Omega and of the partner q (see spread_launch); a 32 x 32
+// tile through LDS, so that every orientation is written along rows.
+__global__ void __launch_bounds__(256) spread_k(double2* X, const int* reps, const int* negs, int nw, int mid, int n,
+                                                int tiles) {
+  __shared__ double2 t[kMir][kMir + 1];
+  const int half = nw - mid, i = blockIdx.y / half, m = mid + blockIdx.y - i * half, mm = nw - 1 - m;
+  const int q = reps ? reps[i] : 0, g = negs ? negs[i] : q;
+  const size_t nn = (size_t)n * n;
+  const double2* S = X + ((size_t)q * nw + m) * nn;
+  const int r0 = blockIdx.x / tiles * kMir, c0 = (blockIdx.x % tiles) * kMir;
+  const int x = threadIdx.x & 31, y0 = threadIdx.x >> 5;
+#pragma unroll
+  for (int y = y0; y < kMir; y += 8)
+    if (r0 + y < n && c0 + x < n) {
+      const double2 v = S[(size_t)(r0 + y) * n + c0 + x];
+      t[y][x] = v;
+      if (g != q) X[((size_t)g * nw + m) * nn + (size_t)(r0 + y) * n + c0 + x] = double2{v.x, -v.y};
+    }
+  if (mm == m) return;
+  __syncthreads();
+#pragma unroll
+  for (int y = y0; y < kMir; y += 8) {
+    const int r = c0 + y, c = r0 + x;
+    if (r >= n || c >= n) continue;
+    const double2 v = t[x][y];
+    X[((size_t)q * nw + mm) * nn + (size_t)r * n + c] = double2{v.x, -v.y};
+    if (g != q) X[((size_t)g * nw + mm) * nn + (size_t)r * n + c] = v;
+  }
+}
+
+hipError_t spread_launch(double2* X, const int* reps, const int* negs, int nq, int nw, int mid, int n, hipStream_t st) {
+  if (nq <= 0 || n <= 0 || mid >= nw) return hipSuccess;
+  const int tiles = (n + kMir - 1) / kMir;
+  const int per = 65535 / (nw - mid);           // q per launch
+  for (int q0 = 0; q0 < nq; q0 += per) {
+    const int cur = std::min(per, nq - q0);
+    spread_k<<<dim3((unsigned)(tiles * tiles), (unsigned)(cur * (nw - mid))), 256, 0, st>>>(
+        X, reps ? reps + q0 : nullptr, negs ? negs + q0 : nullptr, nw, mid, n, tiles);
+  }
+  return hipGetLastError();
+}
+
 // Hermitian part: one thread per entry (r, c) with r <= c of each matrix; it
 // reads both mirror entries and writes both.
 __global__ void herm_avg_k(double2* P, int n) {
@@ -1894,11 +1936,11 @@ hipError_t wtrace_launch(const double2* P, const double2* S, const double2* r, i
 // the rows of the panel, and the trailing updates are GEMMs on the host side.
 // wlu_trsm_upper_k solves one diagonal block of U during back substitution.
 __global__ void __launch_bounds__(256) wlu_init_k(const double2* __restrict__ P0, double2* A,
-                                                   double2* B, int n) {
-  const size_t nn = (size_t)n * n;
-  const double2* P = P0 + blockIdx.x * nn;
+                                                   double2* B, const int* sel, int n) {
+  const size_t nn = (size_t)n * n, at = (size_t)(sel ? sel[blockIdx.x] : blockIdx.x) * nn;
+  const double2* P = P0 + at;
   double2* Am = A + blockIdx.x * nn;
-  double2* Bm = B + blockIdx.x * nn;
+  double2* Bm = B + at;
   for (size_t e = threadIdx.x; e < nn; e += 256) {
     const int r = (int)(e / n), c = (int)(e % n);
     const double2 p = P[e];
@@ -1907,11 +1949,11 @@ __global__ void __launch_bounds__(256) wlu_init_k(const double2* __restrict__ P0
   }
 }
 
-__global__ void __launch_bounds__(256) wlu_panel_k(double2* A, double2* B, int n, int j0, int nb,
+__global__ void __launch_bounds__(256) wlu_panel_k(double2* A, double2* B, const int* sel, int n, int j0, int nb,
                                                     int* flag) {
   const size_t nn = (size_t)n * n;
   double2* Am = A + blockIdx.x * nn;
-  double2* Bm = B + blockIdx.x * nn;
+  double2* Bm = B + (size_t)(sel ? sel[blockIdx.x] : blockIdx.x) * nn;
   const int tid = threadIdx.x, nt = 256;
   __shared__ double sv[256];
   __shared__ int si[256];
@@ -1980,10 +2022,11 @@ __global__ void __launch_bounds__(256) wlu_panel_k(double2* A, double2* B, int n
 }
 
 // rows j0+1 .. j0+nb-1: U12 and B rows of the panel <- L11^{-1} (unit lower)
-__global__ void __launch_bounds__(256) wlu_trsm_lower_k(double2* A, double2* B, int n, int j0, int nb) {
+__global__ void __launch_bounds__(256) wlu_trsm_lower_k(double2* A, double2* B, const int* sel, int n,
+                                                         int j0, int nb) {
   const size_t nn = (size_t)n * n;
   double2* Am = A + blockIdx.x * nn;
-  double2* Bm = B + blockIdx.x * nn;
+  double2* Bm = B + (size_t)(sel ? sel[blockIdx.x] : blockIdx.x) * nn;
   const int j1 = min(j0 + nb, n);
   const int ca = n - j1;               // trailing columns of A
   for (int r = j0 + 1; r < j1; ++r) {
@@ -2004,11 +2047,11 @@ __global__ void __launch_bounds__(256) wlu_trsm_lower_k(double2* A, double2* B, 
 }
 
 // rows j0 .. j1-1 of B <- U11^{-1} B (upper, back substitution within the block)
-__global__ void __launch_bounds__(256) wlu_trsm_upper_k(const double2* A, double2* B, int n, int j0,
-                                                         int nb) {
+__global__ void __launch_bounds__(256) wlu_trsm_upper_k(const double2* A, double2* B, const int* sel,
+                                                         int n, int j0, int nb) {
   const size_t nn = (size_t)n * n;
   const double2* Am = A + blockIdx.x * nn;
-  double2* Bm = B + blockIdx.x * nn;
+  double2* Bm = B + (size_t)(sel ? sel[blockIdx.x] : blockIdx.x) * nn;
   const int j1 = min(j0 + nb, n);
   for (int r = j1 - 1; r >= j0; --r) {
     const double2 d = Am[(size_t)r * n + r];
@@ -2028,15 +2071,15 @@ __global__ void __launch_bounds__(256) wlu_trsm_upper_k(const double2* A, double
   }
 }
 
-hipError_t wlu_launch(int which, const double2* P0, double2* A, double2* B, int n, int j0, int nb,
+hipError_t wlu_launch(int which, const double2* P0, double2* A, double2* B, const int* sel, int n, int j0, int nb,
                       long long nmat, int* flag, hipStream_t st) {
   if (nmat <= 0) return hipSuccess;
   const unsigned g = (unsigned)nmat;
   switch (which) {
-    case 0: wlu_init_k<<<g, 256, 0, st>>>(P0, A, B, n); break;
-    case 1: wlu_panel_k<<<g, 256, 0, st>>>(A, B, n, j0, nb, flag); break;
-    case 2: wlu_trsm_lower_k<<<g, 256, 0, st>>>(A, B, n, j0, nb); break;
-    case 3: wlu_trsm_upper_k<<<g, 256, 0, st>>>(A, B, n, j0, nb); break;
+    case 0: wlu_init_k<<<g, 256, 0, st>>>(P0, A, B, sel, n); break;
+    case 1: wlu_panel_k<<<g, 256, 0, st>>>(A, B, sel, n, j0, nb, flag); break;
+    case 2: wlu_trsm_lower_k<<<g, 256, 0, st>>>(A, B, sel, n, j0, nb); break;
+    case 3: wlu_trsm_upper_k<<<g, 256, 0, st>>>(A, B, sel, n, j0, nb); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
