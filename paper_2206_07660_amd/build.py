@@ -10,7 +10,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgw.so")
-SOURCES = ["gw_kernels.hip", "gw_sandwich.hip", "gw_polar.hip", "gw_dyson.hip", "gw_api.hip", "grids.cpp", "ir.cpp"]
+SOURCES = ["gw_kernels.hip", "gw_sandwich.hip", "gw_polar.hip", "gw_dyson.hip", "gw_wlu.hip", "gw_api.hip", "grids.cpp", "ir.cpp"]
 
 
 def source_hash():
@@ -18,7 +18,7 @@ def source_hash():
     import hashlib
     h = hashlib.sha256()
     for f in ("gw_kernels.hip", "gw_sandwich.hip", "gw_polar.hip", "gw_dyson.hip",
-              "gw_kernels.h", "gw_device.h", "gw_api.hip"):
+              "gw_wlu.hip", "gw_kernels.h", "gw_device.h", "gw_api.hip"):
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

@@ -1430,8 +1430,12 @@ static gw_status solve_core(gw_ctx* c, const gw_z* P0, gw_z* Pt, const int* sel,
   };
   for (int j0 = 0; j0 < n; j0 += kNb) {
     const int j1 = std::min(j0 + kNb, n), w = j1 - j0, rest = n - j1;
-    HIPCHK(c, wlu_launch(1, nullptr, Am, Bm, sel, n, j0, kNb, nmat, c->dflag, c->st));
-    HIPCHK(c, wlu_launch(2, nullptr, Am, Bm, sel, n, j0, kNb, nmat, c->dflag, c->st));
+    if (n - j0 <= 512) {
+      HIPCHK(c, wlu_factor_launch(Am, Bm, sel, n, j0, nmat, c->dflag, c->st));
+    } else {
+      HIPCHK(c, wlu_launch(1, nullptr, Am, Bm, sel, n, j0, kNb, nmat, c->dflag, c->st));
+      HIPCHK(c, wlu_launch(2, nullptr, Am, Bm, sel, n, j0, kNb, nmat, c->dflag, c->st));
+    }
     // A22 -= L21 U12 ;  B2 -= L21 B1
     if ((s = gemm(Am, (long long)j1 * n + j0, Am, (long long)j0 * n + j1, Am, (long long)j1 * n + j1,
                   rest, rest, w)) != GW_OK) return s;
@@ -1441,7 +1445,7 @@ static gw_status solve_core(gw_ctx* c, const gw_z* P0, gw_z* Pt, const int* sel,
   const int nblk = (n + kNb - 1) / kNb;
   for (int b = nblk - 1; b >= 0; --b) {
     const int j0 = b * kNb, w = std::min(kNb, n - j0);
-    HIPCHK(c, wlu_launch(3, nullptr, Am, Bm, sel, n, j0, kNb, nmat, c->dflag, c->st));
+    HIPCHK(c, wlu_back_launch(Am, Bm, sel, n, j0, nmat, c->st));
     // B[0:j0] -= U[0:j0, j0:j0+w] B[j0:j0+w]
     if ((s = gemm(Am, (long long)j0, Bm, (long long)j0 * n, Bm, 0, j0, n, w)) != GW_OK) return s;
   }

@@ -261,5 +261,12 @@ hipError_t sxs_add_launch(const double2* S, const double2* X, double2* Out, int 
 // Pieces of the blocked LU solve of (I - P0) X = P0 for nmat n x n matrices:
 // A holds them one after the other, P0 and B (the solution) have matrix b at
 // position sel[b] (b if sel is null).
+// One panel of 32 columns from j0 (n - j0 <= 512 rows): factorisation, row
+// interchanges and L11^{-1} on the columns right of it and on B; wlu_back_launch
+// applies U11^{-1} to the panel's rows of B.  wlu_launch: 0 sets A = I - P0 and
+// B = P0; 1 and 2 are the panel and its triangular solve for more rows.
+hipError_t wlu_factor_launch(double2* A, double2* B, const int* sel, int n, int j0, long long nmat, int* flag,
+                             hipStream_t st);
+hipError_t wlu_back_launch(const double2* A, double2* B, const int* sel, int n, int j0, long long nmat, hipStream_t st);
 hipError_t wlu_launch(int which, const double2* P0, double2* A, double2* B, const int* sel, int n, int j0, int nb,
                       long long nmat, int* flag, hipStream_t st);

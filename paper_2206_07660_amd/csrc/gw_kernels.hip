@@ -1934,7 +1934,8 @@ hipError_t wtrace_launch(const double2* P, const double2* S, const double2* r, i
 // columns, wlu_panel_k factors the panel with row pivoting (swapping whole
 // rows of A and B), wlu_trsm_lower_k applies the panel's unit-lower block to
 // the rows of the panel, and the trailing updates are GEMMs on the host side.
-// wlu_trsm_upper_k solves one diagonal block of U during back substitution.
+// Used while more than 512 rows remain; wlu_factor_k keeps shorter panels in
+// registers, and wlu_back_k solves the diagonal blocks of U.
 __global__ void __launch_bounds__(256) wlu_init_k(const double2* __restrict__ P0, double2* A,
                                                    double2* B, const int* sel, int n) {
   const size_t nn = (size_t)n * n, at = (size_t)(sel ? sel[blockIdx.x] : blockIdx.x) * nn;
@@ -2046,31 +2047,6 @@ __global__ void __launch_bounds__(256) wlu_trsm_lower_k(double2* A, double2* B, 
   }
 }
 
-// rows j0 .. j1-1 of B <- U11^{-1} B (upper, back substitution within the block)
-__global__ void __launch_bounds__(256) wlu_trsm_upper_k(const double2* A, double2* B, const int* sel,
-                                                         int n, int j0, int nb) {
-  const size_t nn = (size_t)n * n;
-  const double2* Am = A + blockIdx.x * nn;
-  double2* Bm = B + (size_t)(sel ? sel[blockIdx.x] : blockIdx.x) * nn;
-  const int j1 = min(j0 + nb, n);
-  for (int r = j1 - 1; r >= j0; --r) {
-    const double2 d = Am[(size_t)r * n + r];
-    const double den = d.x * d.x + d.y * d.y;
-    const double2 di = den > 0.0 ? double2{d.x / den, -d.y / den} : double2{0.0, 0.0};
-    for (int c = threadIdx.x; c < n; c += 256) {
-      double2 x = Bm[(size_t)r * n + c];
-      for (int i = r + 1; i < j1; ++i) {
-        const double2 u = Am[(size_t)r * n + i];
-        const double2 y = Bm[(size_t)i * n + c];
-        x.x -= u.x * y.x - u.y * y.y;
-        x.y -= u.x * y.y + u.y * y.x;
-      }
-      Bm[(size_t)r * n + c] = double2{x.x * di.x - x.y * di.y, x.x * di.y + x.y * di.x};
-    }
-    __syncthreads();
-  }
-}
-
 hipError_t wlu_launch(int which, const double2* P0, double2* A, double2* B, const int* sel, int n, int j0, int nb,
                       long long nmat, int* flag, hipStream_t st) {
   if (nmat <= 0) return hipSuccess;
@@ -2079,7 +2055,6 @@ hipError_t wlu_launch(int which, const double2* P0, double2* A, double2* B, cons
     case 0: wlu_init_k<<<g, 256, 0, st>>>(P0, A, B, sel, n); break;
     case 1: wlu_panel_k<<<g, 256, 0, st>>>(A, B, sel, n, j0, nb, flag); break;
     case 2: wlu_trsm_lower_k<<<g, 256, 0, st>>>(A, B, sel, n, j0, nb); break;
-    case 3: wlu_trsm_upper_k<<<g, 256, 0, st>>>(A, B, sel, n, j0, nb); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
