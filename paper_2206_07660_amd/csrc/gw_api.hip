@@ -1235,6 +1235,47 @@ static gw_status pol_impl(gw_ctx* c, const Work& w, const void* V, const gw_z* G
   return GW_OK;
 }
 
+// P[tl][Q][Q'] = alpha sum_{k,e} Y[tl][k][Q][e] conj(V[k][Q'][e]) of tcur nodes
+// (added to P with accumulate), completed as pol_finish does; Z has room for
+// the Y of tc nodes.
+static gw_status pol_contract(gw_ctx* c, const char* Y, char* Z, const char* Vq, int tcur, int tc, double2* P,
+                              double2* M, double alpha, bool accumulate, bool herm) {
+  const int nk = c->nk, naux = c->d.naux;
+  const long long n2 = c->n2, sv = c->sv, S = (long long)nk * sv, nn = (long long)naux * naux;
+  const long long room = (long long)tc * S;
+  const double outs = herm ? 0.5 * naux * (naux + 1.0) : (double)nn;
+  if (n2 >= 4 && c->tile_cfg < 0 && room >= tcur * pol_acc_blocks(naux, herm) * 256) {
+    PolAcc a{};
+    a.Y = (const double2*)Y; a.V = (const double2*)Vq;
+    a.P = P; a.M = M; a.part = (double2*)Z;
+    a.nt = tcur; a.naux = naux; a.n2 = (int)n2; a.K = nk * (int)n2;
+    a.tsY = S; a.sv = sv; a.tri = herm; a.accumulate = accumulate;
+    a.alpha = alpha;
+    hipEvent_t e0 = nullptr;
+    gw_status s = prof_begin(c, KC_POL_CONTRACT, &e0);
+    if (s != GW_OK) return s;
+    HIPCHK(c, pol_acc_launch(a, room, c->st));
+    return prof_end(c, KC_POL_CONTRACT, e0, 6.0 * outs * a.K * tcur);
+  }
+  // matrices of one orbital, a chunk without room for the partial sums, or a
+  // tile configuration asked for
+  GemmDesc g = gemm_desc();
+  g.A = Y; g.B = Vq; g.C = P;
+  g.M = naux; g.N = naux; g.K = nk * (int)n2; g.batch = tcur;
+  g.am = aff(n2); g.ak = two((unsigned)n2, 1, sv);
+  g.bk = two((unsigned)n2, 1, sv); g.bn = aff(n2); g.conjB = 1;
+  g.cm = aff(naux); g.cn = aff(1);
+  g.ba = aff(S); g.bb = aff(0); g.bc = aff(nn);
+  g.alpha_r = alpha;
+  if (accumulate) { g.beta_zero = 0; g.beta_r = 1.0; }
+  g.tri = herm ? 1 : 0;
+  g.tag = KC_POL_CONTRACT;
+  gw_status s = run(c, g, Ext{0, (long long)tcur * S}, Ext{0, S}, Ext{0, (long long)tcur * nn});
+  if (s != GW_OK || (!herm && !M)) return s;
+  HIPCHK(c, mirror_launch(P, M, -nn, naux, tcur, herm, c->st));
+  return GW_OK;
+}
+
 static gw_status pol_nodes(gw_ctx* c, const Work& w, const char* Vd, const char* Gd, const char* Gbd, int q,
                            int tb, int te, gw_z* P0, gw_z* M0, bool accumulate, bool herm, const char* Gd2,
                            const char* Gbd2) {
@@ -1275,39 +1316,10 @@ static gw_status pol_nodes(gw_ctx* c, const Work& w, const char* Vd, const char*
         p.accumulate = 1;
         if ((s = sand_prod(c, p, KC_POL_PRODUCER)) != GW_OK) return s;
       }
-      const long long nn = (long long)naux * naux, room = (long long)tc * S;
-      if (n2 >= 4 && c->tile_cfg < 0 && room >= tcur * pol_acc_blocks(naux, herm) * 256) {
-        PolAcc a{};
-        a.Y = (const double2*)X; a.V = (const double2*)Aq;
-        a.P = (double2*)P0 + t0 * nn;
-        a.M = M0 ? (double2*)M0 + (nt - 1 - t0) * nn : nullptr;
-        a.part = (double2*)Z;
-        a.nt = tcur; a.naux = naux; a.n2 = (int)n2; a.K = nk * (int)n2;
-        a.tsY = S; a.sv = sv; a.tri = herm; a.accumulate = accumulate;
-        a.alpha = -(double)c->d.ns / nk;
-        hipEvent_t e0 = nullptr;
-        if ((s = prof_begin(c, KC_POL_CONTRACT, &e0)) != GW_OK) return s;
-        HIPCHK(c, pol_acc_launch(a, room, c->st));
-        const double outs = herm ? 0.5 * naux * (naux + 1.0) : (double)nn;
-        if ((s = prof_end(c, KC_POL_CONTRACT, e0, 6.0 * outs * a.K * tcur)) != GW_OK) return s;
-        continue;
-      }
-      // matrices of one orbital, a chunk without room for the partial sums, or
-      // a tile configuration asked for
-      GemmDesc g = gemm_desc();
-      g.A = X; g.B = Aq; g.C = (double2*)P0 + (long long)t0 * naux * naux;
-      g.M = naux; g.N = naux; g.K = nk * (int)n2; g.batch = tcur;
-      g.am = aff(n2); g.ak = two((unsigned)n2, 1, sv);
-      g.bk = two((unsigned)n2, 1, sv); g.bn = aff(n2); g.conjB = 1;
-      g.cm = aff(naux); g.cn = aff(1);
-      g.ba = aff(S); g.bb = aff(0); g.bc = aff((long long)naux * naux);
-      g.alpha_r = -(double)c->d.ns / nk;
-      if (accumulate) { g.beta_zero = 0; g.beta_r = 1.0; }
-      g.tri = herm ? 1 : 0;
-      g.tag = KC_POL_CONTRACT;
-      if ((s = run(c, g, Ext{0, (long long)tcur * S}, Ext{0, S}, Ext{0, (long long)tcur * naux * naux})) != GW_OK)
-        return s;
-      if ((s = pol_finish(c, P0, M0, t0, t0 + tcur, herm)) != GW_OK) return s;
+      const long long nn = (long long)naux * naux;
+      if ((s = pol_contract(c, X, Z, Aq, tcur, tc, (double2*)P0 + t0 * nn,
+                            M0 ? (double2*)M0 + (nt - 1 - t0) * nn : nullptr, -(double)c->d.ns / nk, accumulate,
+                            herm)) != GW_OK) return s;
       continue;
     }
     // X[tl][k][Q][d][b] = sum_a V[q][k][Q][d][a] G[t0+tl][k+q][a][b]
@@ -1496,6 +1508,27 @@ gw_status gw_screened_W_phi(gw_ctx* c, const gw_z* P0, int nq, gw_z* Pt, double*
 }
 
 // ------------------------------------------------------------- Eq. tilde_sigma2
+// Vt[tl][Q][k][b][j] = sum_Q' M[tl][Q][Q'] V[k][Q'][b][j] for n nodes (M^H
+// with adjoint): the long contraction of the self-energy and of the adjoints.
+static gw_status times_v(gw_ctx* c, const gw_z* M, const gw_z* Vq, char* Vt, int n, bool adjoint) {
+  const int nk = c->nk, naux = c->d.naux;
+  const long long n2 = c->n2, sv = c->sv, S = (long long)nk * sv;
+  GemmDesc g = gemm_desc();
+  g.A = M; g.B = Vq; g.C = Vt;
+  g.M = naux; g.N = nk * (int)n2; g.K = naux; g.batch = n;
+  if (adjoint) { g.am = aff(1); g.ak = aff(naux); g.conjA = 1; } else { g.am = aff(naux); g.ak = aff(1); }
+  g.bk = aff(n2); g.bn = two((unsigned)n2, 1, sv);
+  g.cm = aff((long long)nk * n2); g.cn = aff(1);
+  g.ba = aff((long long)naux * naux); g.bb = aff(0); g.bc = aff(S);
+  // groups of 8 tiles walk every tau: their V tiles and each tau's M
+  // panels stay in L2 (measured at si-4x4x4: fetch 49 -> 29 GB per q,
+  // 25.6 vs 25.9 ms; groups of 16: 21 GB, 26.1 ms)
+  g.batch_fastest = 2;
+  g.group = 8;
+  g.tag = KC_SE_CONTRACT;
+  return run(c, g, Ext{0, (long long)n * naux * naux}, Ext{0, S}, Ext{0, (long long)n * S});
+}
+
 // Contribution of one q at the tau nodes [tb, te); Gd is G in the chain's
 // storage type, Pt the [ntau][naux][naux] array of this q.
 // mirror (fp64): also the contribution of -q at the mirrored nodes, for P~ with
@@ -1542,6 +1575,9 @@ static gw_status se_nodes(gw_ctx* c, const char* Vd, const char* Gd, const gw_z*
       gw_status s = run_split(c, d, Ext{0, (long long)tcur * naux * naux}, Ext{0, (long long)nk * sv},
                               Ext{0, (long long)tcur * S});
       if (s != GW_OK) return s;
+    } else if (!f32) {
+      gw_status s = times_v(c, Pt + (long long)t0 * naux * naux, (const gw_z*)Aq, Vt, tcur, false);
+      if (s != GW_OK) return s;
     } else {
       GemmDesc g = gemm_desc();
       g.A = (const double2*)Pt + (long long)t0 * naux * naux;
@@ -1549,14 +1585,10 @@ static gw_status se_nodes(gw_ctx* c, const char* Vd, const char* Gd, const gw_z*
       g.M = naux; g.N = nk * (int)n2; g.K = naux; g.batch = tcur;
       g.am = aff(naux); g.ak = aff(1);
       g.bk = aff(n2); g.bn = two((unsigned)n2, 1, sv);
-      if (f32) { g.cm = aff(n2); g.cn = two((unsigned)n2, 1, sv); }
-      else { g.cm = aff((long long)nk * n2); g.cn = aff(1); }
+      g.cm = aff(n2); g.cn = two((unsigned)n2, 1, sv);
       g.ba = aff((long long)naux * naux); g.bb = aff(0); g.bc = aff(S);
-      g.ta = 0; g.tb = g.tc = t; g.f32 = t;
-      // groups of 8 tiles walk every tau: their V tiles and each tau's P~
-      // panels stay in L2 (measured at si-4x4x4: fetch 49 -> 29 GB per q,
-      // 25.6 vs 25.9 ms; groups of 16: 21 GB, 26.1 ms)
-      g.batch_fastest = 2;
+      g.ta = 0; g.tb = g.tc = g.f32 = 1;
+      g.batch_fastest = 2;   // as times_v
       g.group = 8;
       g.tag = KC_SE_CONTRACT;
       gw_status s = run(c, g, Ext{0, (long long)tcur * naux * naux}, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * S});
@@ -1872,17 +1904,87 @@ gw_status gw_transform_adjoint(gw_ctx* c, int stat, int inverse, const gw_z* Xin
   return run(c, g, Ext{0, (long long)rows * inner}, Ext{0, batch * inner * R}, Ext{0, batch * rows * R});
 }
 
-// The VJP contractions in every precision: fp64, or in the complex64 modes
-// V complex64, complex64 intermediates, fp32 MFMA (operands rounded on load)
-// with fp64 sums of 512-term chunks for the long contractions, outputs fp64.
-struct VjpMode {
-  int t;        // storage type of V and of the intermediates
-  size_t ez;    // their element size
-  int kchunk;
-};
-static VjpMode vjp_mode(const gw_ctx* c) {
-  const bool f32 = lowp(c);
-  return VjpMode{f32 ? 1 : 0, f32 ? (size_t)8 : (size_t)16, f32 ? kMixedChunk : 0};
+// The fp64 adjoints, one q at a time, on the same kernels as the forward
+// chain; the small matrices of a node meet in one triple product each:
+//   Gbar(t)[k]   += -(1/nk) sum_Q V_Q Sbar(t)[k+q] Vt_Q^H,   Vt = P~(t) V
+//   Ptbar(t)[Q][Q'] = -(1/nk) sum_{k,e} (G^H V_Q Sbar[k+q])[e] conj(V_Q'[e])
+// pair: also the first of these for -q at the mirrored nodes, from the same Vt
+// (see se_nodes):
+//   Gbar(beta - t)[k+q] += -(1/nk) sum_Q V_Q^H Sbar(beta - t)[k] Vt_Q.
+static gw_status se_vjp_g(gw_ctx* c, const gw_z* Vq, const gw_z* Pt, const gw_z* Sbar, int q, int te, gw_z* Gbar,
+                          bool pair) {
+  const int tc = c->tc, nk = c->nk, nt = c->d.ntau;
+  const long long n2 = c->n2, sv = c->sv, S = (long long)nk * sv, gs = (long long)nk * n2;
+  char* Vt = (char*)c->ws;
+  for (int t0 = 0; t0 < te; t0 += tc) {
+    const int tcur = std::min(tc, te - t0);
+    gw_status s = times_v(c, Pt + (long long)t0 * c->d.naux * c->d.naux, Vq, Vt, tcur, false);
+    if (s != GW_OK) return s;
+    SandSum x{};
+    x.A = Vq; x.skA = sv; x.sqA = n2;
+    x.B = Vt; x.tsB = S; x.skB = n2; x.sqB = gs;
+    x.tab = c->dplus + (size_t)q * nk;
+    x.nt = tcur; x.alpha = -1.0 / nk; x.accumulate = 1;
+    x.part = (double2*)((char*)c->ws + region_bytes(c, tc)); x.part_elems = (long long)tc * S;
+    x.bh = 1;
+    x.G = (const double2*)Sbar + t0 * gs; x.tsG = gs; x.tabG = 1;
+    x.O = (double2*)Gbar + t0 * gs; x.tsO = gs;
+    if ((s = sand_sum(c, x, KC_SE_FINAL)) != GW_OK) return s;
+    if (!pair) continue;
+    x.bh = 0;
+    x.G = (const double2*)Sbar + (nt - 1 - t0) * gs; x.tsG = -gs; x.tabG = 0;
+    x.O = (double2*)Gbar + (nt - 1 - t0) * gs; x.tsO = -gs; x.tabO = 1;
+    if ((s = sand_sum(c, x, KC_SE_FINAL)) != GW_OK) return s;
+  }
+  return GW_OK;
+}
+
+static gw_status se_vjp_p(gw_ctx* c, const gw_z* Vq, const gw_z* G, const gw_z* Sbar, int q, gw_z* Ptbar) {
+  const int tc = c->tc, nk = c->nk, nt = c->d.ntau;
+  const long long gs = (long long)nk * c->n2, S = (long long)nk * c->sv;
+  for (int t0 = 0; t0 < nt; t0 += tc) {
+    const int tcur = std::min(tc, nt - t0);
+    SandProd p{};
+    p.V = (const double2*)Vq; p.Y = (double2*)c->ws; p.tab = c->dplus + (size_t)q * nk;
+    p.nt = tcur; p.tsY = S;
+    p.L = (const double2*)G + t0 * gs; p.tsL = gs; p.hermL = 1;
+    p.R = (const double2*)Sbar + t0 * gs; p.tsR = gs; p.tabR = 1;
+    gw_status s = sand_prod(c, p, KC_SE_PRODUCER);
+    if (s != GW_OK) return s;
+    if ((s = pol_contract(c, (char*)c->ws, (char*)c->ws + region_bytes(c, tc), (const char*)Vq, tcur, tc,
+                          (double2*)Ptbar + (long long)t0 * c->d.naux * c->d.naux, nullptr, -1.0 / nk, false, false)) != GW_OK)
+      return s;
+  }
+  return GW_OK;
+}
+
+// Both slots of the polarization at the nodes [0, te):
+//   Gbar(t)[k+q]        += sc sum_Q V_Q^H G(beta - t)[k]^H (P0bar V)_Q
+//   Gbar(beta - t)[k]   += sc sum_Q V_Q G(t)[k+q]^H (P0bar^H V)_Q^H
+static gw_status pol_vjp_q(gw_ctx* c, const gw_z* Vq, const gw_z* G, const gw_z* P0bar, int q, int te, gw_z* Gbar) {
+  const int tc = c->tc, nk = c->nk, nt = c->d.ntau;
+  const long long n2 = c->n2, sv = c->sv, S = (long long)nk * sv, gs = (long long)nk * n2;
+  for (int t0 = 0; t0 < te; t0 += tc) {
+    const int tcur = std::min(tc, te - t0);
+    const gw_z* Pb = P0bar + (long long)t0 * c->d.naux * c->d.naux;
+    gw_status s = times_v(c, Pb, Vq, (char*)c->ws, tcur, false);
+    if (s != GW_OK) return s;
+    SandSum x{};
+    x.A = Vq; x.skA = sv; x.sqA = n2;
+    x.B = c->ws; x.tsB = S; x.skB = n2; x.sqB = gs;
+    x.tab = c->dplus + (size_t)q * nk;
+    x.nt = tcur; x.alpha = -(double)c->d.ns / nk; x.accumulate = 1; x.hermG = 1;
+    x.part = (double2*)((char*)c->ws + region_bytes(c, tc)); x.part_elems = (long long)tc * S;
+    x.G = (const double2*)G + (nt - 1 - t0) * gs; x.tsG = -gs;
+    x.O = (double2*)Gbar + t0 * gs; x.tsO = gs; x.tabO = 1;
+    if ((s = sand_sum(c, x, KC_SE_FINAL)) != GW_OK) return s;
+    if ((s = times_v(c, Pb, Vq, (char*)c->ws, tcur, true)) != GW_OK) return s;
+    x.bh = 1;
+    x.G = (const double2*)G + t0 * gs; x.tsG = gs; x.tabG = 1;
+    x.O = (double2*)Gbar + (nt - 1 - t0) * gs; x.tsO = -gs; x.tabO = 0;
+    if ((s = sand_sum(c, x, KC_SE_FINAL)) != GW_OK) return s;
+  }
+  return GW_OK;
 }
 
 gw_status gw_self_energy_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_z* Pt,
@@ -1897,12 +1999,21 @@ gw_status gw_self_energy_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_z
     return fail(c, GW_ERR_WORKSPACE, "self-energy workspace too small");
   const int nk = c->nk, nao = c->d.nao, naux = c->d.naux, nt = c->d.ntau;
   const long long n2 = c->n2, sv = c->sv, S = (long long)nk * sv;
-  const VjpMode vm = vjp_mode(c);
-  const int t = vm.t;
+  if (!lowp(c)) {
+    const long long per = (long long)nt * naux * naux;
+    for (int q = q0; q < q0 + nq; ++q) {
+      const gw_z* Vq = (const gw_z*)V + (size_t)q * S;
+      if ((s = se_vjp_g(c, Vq, Pt + (q - q0) * per, Sbar, q, nt, Gbar, false)) != GW_OK) return s;
+      if ((s = se_vjp_p(c, Vq, G, Sbar, q, Ptbar + (q - q0) * per)) != GW_OK) return s;
+    }
+    return GW_OK;
+  }
+  // the complex64 modes: complex64 intermediates, fp32 MFMA (operands rounded
+  // on load) with fp64 sums of 512-term chunks for the long contractions
   char* R0 = (char*)c->ws;
   char* R1 = (char*)c->ws + region_bytes(c, tc);
   for (int q = q0; q < q0 + nq; ++q) {
-    const char* Aq = (const char*)V + (size_t)q * nk * sv * vm.ez;
+    const char* Aq = (const char*)V + (size_t)q * S * 8;
     for (int t0 = 0; t0 < nt; t0 += tc) {
       const int tcur = std::min(tc, nt - t0);
       const gw_z* Ptq = Pt + ((long long)(q - q0) * nt + t0) * naux * naux;
@@ -1913,7 +2024,7 @@ gw_status gw_self_energy_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_z
       g.am = aff(naux); g.ak = aff(1); g.bk = aff(n2); g.bn = two((unsigned)n2, 1, sv);
       g.cm = aff((long long)nk * n2); g.cn = aff(1);
       g.ba = aff((long long)naux * naux); g.bb = aff(0); g.bc = aff(S);
-      g.ta = 0; g.tb = g.tc = t; g.f32 = t;
+      g.ta = 0; g.tb = g.tc = g.f32 = 1;
       g.batch_fastest = 1;
       g.tag = KC_SE_CONTRACT;
       if ((s = run(c, g, Ext{0, (long long)tcur * naux * naux}, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * S})) != GW_OK) return s;
@@ -1925,7 +2036,7 @@ gw_status gw_self_energy_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_z
       g.cm = aff(nao); g.cn = two(nao, 1, S);
       g.ba = aff(sv); g.bb = aff(0); g.bc = aff(sv);
       g.tab = c->dplus + (size_t)q * nk; g.tmod = nk; g.tsB = n2;
-      g.ta = g.tc = t; g.tb = 0; g.f32 = t;
+      g.ta = g.tc = g.f32 = 1; g.tb = 0;
       g.tag = KC_SE_PRODUCER;
       if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * nk * n2}, Ext{0, (long long)tcur * S})) != GW_OK) return s;
       // Gbar[t][kk][a][b] += -(1/nk) sum_{Q,j} L'[tl][kk][Q][a][j] conj(Vt[tl][Q][kk][b][j])
@@ -1937,7 +2048,7 @@ gw_status gw_self_energy_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_z
       g.cm = aff(nao); g.cn = aff(1);
       g.ba = two(nk, sv, S); g.bb = two(nk, n2, S); g.bc = two(nk, n2, (long long)nk * n2);
       g.alpha_r = -1.0 / nk; g.beta_zero = 0; g.beta_r = 1.0;
-      g.ta = g.tb = t; g.tc = 0; g.f32 = t; g.kchunk = vm.kchunk;
+      g.ta = g.tb = g.f32 = 1; g.tc = 0; g.kchunk = kMixedChunk;
       g.tag = KC_SE_FINAL;
       if ((s = run(c, g, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * nk * n2})) != GW_OK) return s;
       // R0 = Y[tl][kk][Q'][a][j] = sum_b G[t][kk][a][b] V[q][kk][Q'][b][j]
@@ -1948,7 +2059,7 @@ gw_status gw_self_energy_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_z
       g.bk = aff(nao); g.bn = two(nao, 1, n2);
       g.cm = two(nao, nao, S); g.cn = two(nao, 1, n2);
       g.ba = aff(n2); g.bb = aff(sv); g.bc = aff(sv);
-      g.ta = 0; g.tb = g.tc = t; g.f32 = t;
+      g.ta = 0; g.tb = g.tc = g.f32 = 1;
       g.tag = KC_SE_PRODUCER;
       if ((s = run(c, g, Ext{0, (long long)tcur * nk * n2}, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * S})) != GW_OK) return s;
       // Ptbar[q][t][Q][Q'] = -(1/nk) sum_{kk,a,j} L'[tl][kk][Q][a][j] conj(Y[tl][kk][Q'][a][j])
@@ -1960,7 +2071,7 @@ gw_status gw_self_energy_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_z
       g.cm = aff(naux); g.cn = aff(1);
       g.ba = aff(S); g.bb = aff(S); g.bc = aff((long long)naux * naux);
       g.alpha_r = -1.0 / nk;
-      g.ta = g.tb = t; g.tc = 0; g.f32 = t; g.kchunk = vm.kchunk;
+      g.ta = g.tb = g.f32 = 1; g.tc = 0; g.kchunk = kMixedChunk;
       g.tag = KC_POL_CONTRACT;
       if ((s = run(c, g, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * naux * naux})) != GW_OK) return s;
     }
@@ -1981,12 +2092,18 @@ gw_status gw_polarization_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_
   const int nk = c->nk, nao = c->d.nao, naux = c->d.naux, nt = c->d.ntau;
   const long long n2 = c->n2, sv = c->sv, S = (long long)nk * sv;
   const double sc = -(double)c->d.ns / nk;
-  const VjpMode vm = vjp_mode(c);
-  const int t = vm.t;
+  if (!lowp(c)) {
+    for (int q = q0; q < q0 + nq; ++q)
+      if ((s = pol_vjp_q(c, (const gw_z*)V + (size_t)q * S, G, P0bar + (long long)(q - q0) * nt * naux * naux, q, nt,
+                         Gbar)) != GW_OK) return s;
+    return GW_OK;
+  }
+  // the complex64 modes: complex64 intermediates, fp32 MFMA (operands rounded
+  // on load) with fp64 sums of 512-term chunks for the long contractions
   char* R0 = (char*)c->ws;
   char* R1 = (char*)c->ws + region_bytes(c, tc);
   for (int q = q0; q < q0 + nq; ++q) {
-    const char* Aq = (const char*)V + (size_t)q * nk * sv * vm.ez;
+    const char* Aq = (const char*)V + (size_t)q * S * 8;
     for (int t0 = 0; t0 < nt; t0 += tc) {
       const int tcur = std::min(tc, nt - t0);
       const gw_z* Pb = P0bar + ((long long)(q - q0) * nt + t0) * naux * naux;
@@ -1999,7 +2116,7 @@ gw_status gw_polarization_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_
       g.bk = aff(nao); g.bn = two(nao, 1, n2);
       g.cm = two(nao, nao, S); g.cn = two(nao, 1, n2);
       g.ba = aff(n2); g.bb = aff(sv); g.bc = aff(sv);
-      g.ta = 0; g.tb = g.tc = t; g.f32 = t;
+      g.ta = 0; g.tb = g.tc = g.f32 = 1;
       g.tag = KC_POL_PRODUCER;
       if ((s = run(c, g, Ext{-(long long)(tcur - 1) * nk * n2, (long long)nk * n2}, Ext{0, (long long)nk * sv}, Ext{0, (long long)tc * S})) != GW_OK) return s;
       // R0 = U[tl][Q][k][e] = sum_Q' Pbar[Q][Q'] W[tl][k][Q'][e]
@@ -2009,7 +2126,7 @@ gw_status gw_polarization_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_
       g.am = aff(naux); g.ak = aff(1); g.bk = aff(n2); g.bn = two((unsigned)n2, 1, sv);
       g.cm = aff((long long)nk * n2); g.cn = aff(1);
       g.ba = aff((long long)naux * naux); g.bb = aff(S); g.bc = aff(S);
-      g.ta = 0; g.tb = g.tc = t; g.f32 = t;
+      g.ta = 0; g.tb = g.tc = g.f32 = 1;
       g.tag = KC_SE_CONTRACT;
       if ((s = run(c, g, Ext{0, (long long)tcur * naux * naux}, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * S})) != GW_OK) return s;
       // Gbar[t0+tl][k+q][a][b] += sc sum_{Q,d} conj(V[q][k][Q][d][a]) U[tl][Q][k][d][b]
@@ -2022,7 +2139,7 @@ gw_status gw_polarization_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_
       g.ba = two(nk, sv, 0); g.bb = two(nk, n2, S); g.bc = two(nk, 0, (long long)nk * n2);
       g.tab = c->dplus + (size_t)q * nk; g.tmod = nk; g.tsC = n2;
       g.alpha_r = sc; g.beta_zero = 0; g.beta_r = 1.0;
-      g.ta = g.tb = t; g.tc = 0; g.f32 = t; g.kchunk = vm.kchunk;
+      g.ta = g.tb = g.f32 = 1; g.tc = 0; g.kchunk = kMixedChunk;
       g.tag = KC_SE_FINAL;
       if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * nk * n2})) != GW_OK) return s;
       // --- mirrored slot: Gbar[nt-1-t][k] += sc sum_{Q',b} V[q][k][Q'][c][b] T[Q'][k][d][b]
@@ -2034,7 +2151,7 @@ gw_status gw_polarization_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_
       g.cm = aff(nao); g.cn = two(nao, 1, S);
       g.ba = aff(sv); g.bb = aff(0); g.bc = aff(sv);
       g.tab = c->dplus + (size_t)q * nk; g.tmod = nk; g.tsB = n2;
-      g.ta = g.tc = t; g.tb = 0; g.f32 = t;
+      g.ta = g.tc = g.f32 = 1; g.tb = 0;
       g.tag = KC_POL_PRODUCER;
       if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * nk * n2}, Ext{0, (long long)tc * S})) != GW_OK) return s;
       // R0 = T[tl][Q'][k][e] = sum_Q Pbar[Q][Q'] conj(X[tl][k][Q][e])
@@ -2044,7 +2161,7 @@ gw_status gw_polarization_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_
       g.am = aff(1); g.ak = aff(naux); g.bk = aff(n2); g.bn = two((unsigned)n2, 1, sv); g.conjB = 1;
       g.cm = aff((long long)nk * n2); g.cn = aff(1);
       g.ba = aff((long long)naux * naux); g.bb = aff(S); g.bc = aff(S);
-      g.ta = 0; g.tb = g.tc = t; g.f32 = t;
+      g.ta = 0; g.tb = g.tc = g.f32 = 1;
       g.tag = KC_SE_CONTRACT;
       if ((s = run(c, g, Ext{0, (long long)tcur * naux * naux}, Ext{0, (long long)tcur * S}, Ext{0, (long long)tcur * S})) != GW_OK) return s;
       // Gbar[nt-1-t0-tl][k][c][d] += sc sum_{Q',b} V[q][k][Q'][c][b] T[tl][Q'][k][d][b]
@@ -2056,7 +2173,7 @@ gw_status gw_polarization_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_
       g.cm = aff(nao); g.cn = aff(1);
       g.ba = two(nk, sv, 0); g.bb = two(nk, n2, S); g.bc = two(nk, n2, -(long long)nk * n2);
       g.alpha_r = sc; g.beta_zero = 0; g.beta_r = 1.0;
-      g.ta = g.tb = t; g.tc = 0; g.f32 = t; g.kchunk = vm.kchunk;
+      g.ta = g.tb = g.f32 = 1; g.tc = 0; g.kchunk = kMixedChunk;
       g.tag = KC_SE_FINAL;
       if ((s = run(c, g, Ext{0, (long long)nk * sv}, Ext{0, (long long)tcur * S}, Ext{-(long long)(tcur - 1) * nk * n2, (long long)nk * n2})) != GW_OK) return s;
     }
@@ -2518,10 +2635,50 @@ gw_status gw_sigma_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_z* Pt_t
   const int nk = c->nk, nt = c->d.ntau, nwb = c->d.nw_b;
   const long long nn = (long long)c->d.naux * c->d.naux;
   if ((s = zero_z(c, G_bar, (long long)nt * nk * c->n2)) != GW_OK) return s;
+  if (!lowp(c)) {
+    // P0^{-q}(beta - tau) = P0^q(tau)^T for any G (see pol_impl), so the
+    // cotangents of q and -q add up, P0bar^q(tau) + P0bar^{-q}(beta - tau)^T,
+    // before one polarization adjoint for both (half of the nodes for q = -q).
+    // With pairs_ok the P~ V of -q comes from that of q as in se_nodes.
+    // Measured with the triple products, 3x3x3, nao 16, naux 150: 249 -> 111 ms.
+    const bool pairs = pairs_ok(c, GW_HERM_FORWARD);
+    const long long per = nt * nn;
+    // from P~bar(tau) in place to P0bar(tau)
+    auto back = [&](gw_z* P, const gw_z* pw) -> gw_status {
+      gw_status r;
+      if ((r = gw_transform_adjoint(c, GW_BOSON, 1, P, 1, nn, p.w2)) != GW_OK) return r;
+      if ((r = gw_screened_W_lin(c, pw, p.w2, 1, 1, p.w3)) != GW_OK) return r;
+      return gw_transform_adjoint(c, GW_BOSON, 0, p.w3, 1, nn, P);
+    };
+    for (int q = 0; q < nk; ++q) {
+      const int m = c->neg[q];
+      if (m < q) continue;
+      for (int half = 0; half < (m == q ? 1 : 2); ++half) {
+        const int z = half ? m : q;
+        const gw_z* Vz = (const gw_z*)V + (size_t)z * nk * c->sv;
+        gw_z* Pb = half ? p.ta : p.tb;               // p.ta is free once P~ V is done
+        if (!stored && (s = pt_one_q(c, V, G, z, p, nullptr, pairs)) != GW_OK) return s;
+        const gw_z* pt = stored ? Pt_tau + (size_t)z * per : p.ta;
+        const gw_z* pw = stored ? Pt_iw + (size_t)z * nwb * nn : p.w1;
+        if (!half || !pairs) {
+          const bool self = m == q;
+          if ((s = se_vjp_g(c, Vz, pt, Stau_bar, z, pairs && self ? nt / 2 : nt, G_bar, pairs)) != GW_OK) return s;
+        }
+        if ((s = se_vjp_p(c, Vz, G, Stau_bar, z, Pb)) != GW_OK) return s;
+        if ((s = back(Pb, pw)) != GW_OK) return s;
+      }
+      const gw_z* Vq = (const gw_z*)V + (size_t)q * nk * c->sv;
+      const int te = m == q ? nt / 2 : nt;
+      HIPCHK(c, add_transpose_launch((double2*)p.tb, (double2*)(m == q ? p.tb : p.ta) + (nt - 1) * nn, c->d.naux, te,
+                                     c->st));
+      if ((s = pol_vjp_q(c, Vq, G, p.tb, q, te, G_bar)) != GW_OK) return s;
+    }
+    return gw_hf_vjp(c, V, Sinf_bar, G_bar);
+  }
   for (int q = 0; q < nk; ++q) {
     const gw_z* pt = stored ? Pt_tau + (size_t)q * nt * nn : p.ta;
     const gw_z* pw = stored ? Pt_iw + (size_t)q * nwb * nn : p.w1;
-    if (!stored && (s = pt_one_q(c, V, G, q, p, nullptr, pairs_ok(c, GW_HERM_FORWARD))) != GW_OK) return s;
+    if (!stored && (s = pt_one_q(c, V, G, q, p, nullptr, false)) != GW_OK) return s;
     // Sigma~ = SE[P~, G]: G part into G_bar, P~ part into P_bar (p.tb)
     if ((s = gw_self_energy_vjp(c, V, G, pt, Stau_bar, q, 1, G_bar, p.tb)) != GW_OK) return s;
     // back through i Omega -> tau, the screened-interaction solve, tau -> i Omega

@@ -241,6 +241,9 @@ hipError_t wtrace_launch(const double2* P, const double2* S, const double2* r, i
 // transpose of the (completed) matrix.
 hipError_t mirror_launch(double2* src, double2* dst, long long dstep, int n, long long nmat, bool herm,
                          hipStream_t st);
+// dst[b] += src[-b]^T for b < nmat (n x n, row-major, one after the other; src
+// points at the matrix of b = 0).
+hipError_t add_transpose_launch(double2* dst, const double2* src, int n, long long nmat, hipStream_t st);
 // X(-Omega) = X(Omega)^H and, for the partner -q, X^{-q}(Omega) = conj(X^q(Omega))
 // written from the matrices at Omega >= 0: for i < nq and mid <= m < nw the
 // matrix at X + (q nw + m) n^2, q = reps[i] (0 if reps is null), fills (q, nw-1-m)
