@@ -233,7 +233,7 @@ gw_status run(gw_ctx* c, const GemmDesc& g, Ext eA, Ext eB, Ext eC) {
   // polarization contraction, 64x96 on the three-product (Gauss) form for
   // the self-energy one
   if (g.tag == KC_POL_PRODUCER || g.tag == KC_SE_PRODUCER) gg.cfg = c->prod_tiles;
-  else gg.cfg = c->tile_cfg >= 0 ? c->tile_cfg : (g.tag == KC_SE_CONTRACT ? 7 : 0);
+  else gg.cfg = c->tile_cfg >= 0 ? c->tile_cfg : (g.tag == KC_SE_CONTRACT ? ((g.M - 1) % 64 < 32 ? 10 : 7) : 0);
   hipError_t e = zgemm_launch(gg, c->st);
   if (e != hipSuccess) return fail(c, GW_ERR_DEVICE, std::string("zgemm: ") + hipGetErrorString(e));
   // MFMA flops executed: 8 real flops per complex multiply-add, 6 on the

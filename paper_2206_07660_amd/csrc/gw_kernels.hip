@@ -212,6 +212,9 @@ __global__ void __launch_bounds__(64 * WM * WN * WK) zgemm_k(GemmDesc d) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) sumR[i][j][r] = sumI[i][j][r] = 0.0;
   }
+  const S sa = d.conjA ? S(-1) : S(1);
+  const S sb = d.conjB ? S(-1) : S(1);
+  const double sab = d.conjA != d.conjB ? -1.0 : 1.0;   // sign of the Im Im products of an M3 loop
   auto promote = [&]() {
     if constexpr (F32) {
 #pragma unroll
@@ -221,7 +224,7 @@ __global__ void __launch_bounds__(64 * WM * WN * WK) zgemm_k(GemmDesc d) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             if constexpr (M3) {
-              const double p1 = accR[i][j][r], p2 = accN[i][j][r], p3 = accI[i][j][r];
+              const double p1 = accR[i][j][r], p2 = sab * accN[i][j][r], p3 = accI[i][j][r];
               sumR[i][j][r] += p1 - p2;
               sumI[i][j][r] += p3 - p1 - p2;
             } else {
@@ -238,8 +241,6 @@ __global__ void __launch_bounds__(64 * WM * WN * WK) zgemm_k(GemmDesc d) {
 
   const unsigned K = (unsigned)d.K;
   const unsigned kstep = 4u * WK;
-  const S sa = d.conjA ? S(-1) : S(1);
-  const S sb = d.conjB ? S(-1) : S(1);
   const S2 zero2 = S2{0, 0};
 
   // Branch-free fragment loads: an out-of-range lane reads the operand's first
@@ -387,6 +388,24 @@ __global__ void __launch_bounds__(64 * WM * WN * WK) zgemm_k(GemmDesc d) {
       ub.b = adv ? nb.b : ub.b;
     };
     auto mmf = [&](const S2 (&a)[BM], const S2 (&b)[BN]) {
+      if constexpr (M3) {
+        // conjugations enter through the sums and the combination (res), not
+        // as sign flips: vector instructions take the MFMAs' time
+        S as[BM], bs[BN];
+#pragma unroll
+        for (int i = 0; i < BM; ++i) as[i] = fma(sa, a[i].y, a[i].x);
+#pragma unroll
+        for (int j = 0; j < BN; ++j) bs[j] = fma(sb, b[j].y, b[j].x);
+#pragma unroll
+        for (int i = 0; i < BM; ++i)
+#pragma unroll
+          for (int j = 0; j < BN; ++j) {
+            accR[i][j] = MM::run(a[i].x, b[j].x, accR[i][j]);
+            accN[i][j] = MM::run(a[i].y, b[j].y, accN[i][j]);
+            accI[i][j] = MM::run(as[i], bs[j], accI[i][j]);
+          }
+        return;
+      }
       S ar[BM], ai[BM], br[BN], bi[BN];
 #pragma unroll
       for (int i = 0; i < BM; ++i) {
@@ -397,22 +416,6 @@ __global__ void __launch_bounds__(64 * WM * WN * WK) zgemm_k(GemmDesc d) {
       for (int j = 0; j < BN; ++j) {
         br[j] = b[j].x;
         bi[j] = flip(b[j].y, mb);
-      }
-      if constexpr (M3) {
-        S as[BM], bs[BN];
-#pragma unroll
-        for (int i = 0; i < BM; ++i) as[i] = ar[i] + ai[i];
-#pragma unroll
-        for (int j = 0; j < BN; ++j) bs[j] = br[j] + bi[j];
-#pragma unroll
-        for (int i = 0; i < BM; ++i)
-#pragma unroll
-          for (int j = 0; j < BN; ++j) {
-            accR[i][j] = MM::run(ar[i], br[j], accR[i][j]);
-            accN[i][j] = MM::run(ai[i], bi[j], accN[i][j]);
-            accI[i][j] = MM::run(as[i], bs[j], accI[i][j]);
-          }
-        return;
       }
 #pragma unroll
       for (int i = 0; i < BM; ++i)
@@ -503,7 +506,7 @@ __global__ void __launch_bounds__(64 * WM * WN * WK) zgemm_k(GemmDesc d) {
   auto res = [&](int i, int j, int r, bool im) -> double {
     if constexpr (F32) return im ? sumI[i][j][r] : sumR[i][j][r];   // M3 combined in promote
     else if constexpr (M3)
-      return im ? accI[i][j][r] - accR[i][j][r] - accN[i][j][r] : accR[i][j][r] - accN[i][j][r];
+      return im ? accI[i][j][r] - accR[i][j][r] - sab * accN[i][j][r] : accR[i][j][r] - sab * accN[i][j][r];
     else return im ? accI[i][j][r] : accR[i][j][r];
   };
 
@@ -856,12 +859,22 @@ static hipError_t launch_cfg(const GemmDesc& d0, hipStream_t st) {
 // the configuration in d.cfg
 // (0: 64x64, 1: 64x128, 2: 128x64, 3: 128x64 on eight waves, 4: 64x64 with
 // two-way split K; 5..9 the three-product form on 64x64, 64x128, 64x96,
-// 128x64 on eight waves, 128x64).  Measured at si-4x4x4 (ms per q, fp64):
+// 128x64 on eight waves, 128x64; 10: 32x192, for a last 64-row tile at most
+// half full: naux 150 at 3x3x3, nao 16, 60 nodes 955 vs 1125 us per q (7)).  Measured at si-4x4x4 (ms per q, fp64):
 // polarization 22.6 (0) vs 23.3 (5), 28.0 (4); self-energy 31.7 (1) vs 25.7
 // (7), 27.2 (5), 28.6 (8), 34.5 (6), 35.2 (9) -- 6 and 9 need more than 256
 // VGPRs and run one wave per SIMD; loads two K-steps ahead (a third register
 // stage) gained nothing on either.  The producers (K = nao) gain nothing
 // from the three-product form (11.7 vs 12.0 ms), their stores bound them.
+// Whether the last 64-row tile of M rows is at most half full.
+static bool half_rows(int M) { return (M - 1) % 64 < 32; }
+// Whether 32 x 32 tiles execute less than 0.8 of what 64 x 64 tiles do of a
+// triangle; the smaller tiles read their operands twice as often.
+static bool small_triangle(int tri, int M) {
+  const long long b = (M + 31) / 32, t = (M + 63) / 64;
+  return tri && 5 * b * (b + 1) < 16 * t * (t + 1);
+}
+
 template <int TAG, class TA, class TB, class TC, bool F32>
 static hipError_t launch_typed(const GemmDesc& d, hipStream_t st) {
   // nao <= 16: one 16 x 16 block per workgroup instead of four, three of them
@@ -881,6 +894,7 @@ static hipError_t launch_typed(const GemmDesc& d, hipStream_t st) {
       case 7: return launch_cfg<2, 2, 1, 2, 3, TAG, TA, TB, TC, F32, true>(d, st);
       case 8: return launch_cfg<4, 2, 1, 2, 2, TAG, TA, TB, TC, F32, true>(d, st);
       case 9: return launch_cfg<2, 2, 1, 4, 2, TAG, TA, TB, TC, F32, true>(d, st);
+      case 10: return launch_cfg<1, 4, 1, 2, 3, TAG, TA, TB, TC, F32, true>(d, st);
       default: break;
     }
   }
@@ -892,7 +906,15 @@ static hipError_t launch_typed(const GemmDesc& d, hipStream_t st) {
   // 19.9-20.3 vs 23.1 ms per q, the polarization one (default 0) four, 19.1
   // vs 19.9 ms.
   if constexpr ((TAG == KC_POL_CONTRACT || TAG == KC_SE_CONTRACT) && F32) {
-    if (d.cfg >= 5 && d.cfg <= 9) return launch_cfg<2, 2, 2, 2, 2, TAG, TA, TB, TC, F32, true>(d, st);
+    // 32-row tiles where 64-row ones would be half empty, with the same sums
+    // (3x3x3, nao 16, naux 150, 60 nodes, us per q: self-energy 913 -> 724,
+    // polarization 1607 -> 946)
+    if constexpr (TAG == KC_SE_CONTRACT) {
+      if (d.cfg >= 5 && d.cfg <= 10 && half_rows(d.M)) return launch_cfg<1, 2, 2, 2, 2, TAG, TA, TB, TC, F32, true>(d, st);
+    } else {
+      if (small_triangle(d.tri, d.M)) return launch_cfg<1, 1, 2, 2, 2, TAG, TA, TB, TC, F32>(d, st);
+    }
+    if (d.cfg >= 5 && d.cfg <= 10) return launch_cfg<2, 2, 2, 2, 2, TAG, TA, TB, TC, F32, true>(d, st);
     return launch_cfg<2, 2, 2, 2, 2, TAG, TA, TB, TC, F32>(d, st);
   }
   // the producers (K = nao): fp32 MFMA (complex64 intermediates) on the
@@ -940,7 +962,7 @@ static hipError_t launch_tag(const GemmDesc& d, hipStream_t st) {
 
 bool zgemm_three_product(const GemmDesc& d) {
   if (d.tag != KC_POL_CONTRACT && d.tag != KC_SE_CONTRACT) return false;
-  if (d.cfg < 5 || d.cfg > 9 || (d.M <= 32 && d.N <= 32)) return false;
+  if (d.cfg < 5 || d.cfg > 10 || (d.M <= 32 && d.N <= 32)) return false;
   // the fp32 tile splits K over two waves: K-steps of 8
   return uniform_k(d, d.f32 ? 8u : 4u, d.ta ? 8 : 16, d.tb ? 8 : 16);
 }
@@ -1326,8 +1348,12 @@ hipError_t bsgemm_launch(const SplitDesc& d, hipStream_t st) {
     return hipErrorInvalidValue;
   }
   if (d.nsplit != 2) return hipErrorInvalidValue;
-  if (d.tag == KC_POL_CONTRACT && d.ta == 1 && d.tb == 1 && d.tc == 0)
+  if (d.tag == KC_POL_CONTRACT && d.ta == 1 && d.tb == 1 && d.tc == 0) {
+    // half-empty tiles on the diagonal and at the edge: 32 x 32 ones (naux 150
+    // at 3x3x3, nao 16, 60 nodes: 406 -> 337 us per q; the same sums)
+    if (small_triangle(d.tri, d.M)) return bs_cfg<1, 1, 2, 2, KC_POL_CONTRACT, float2, float2, double2, true, true, true, float, 2>(d, st);
     return bs_cfg<2, 2, 2, 2, KC_POL_CONTRACT, float2, float2, double2, true, true, true, float, 2>(d, st);
+  }
   if (d.tag == KC_SE_CONTRACT && d.ta == 1 && d.tb == 1 && d.tc == 1) {
     if (d.K > d.kchunk)
       return bs_cfg<2, 2, 2, 2, KC_SE_CONTRACT, float2, float2, float2, true, true, false, double, 2>(d, st);

@@ -238,8 +238,10 @@ __global__ void __launch_bounds__(64 * W) pol_acc_k(PolAcc d) {
     // No branch around single loads (each would wait for the one before); the
     // last ones go unused.
     auto turn = [&](int s) {
+      __builtin_amdgcn_s_setprio(3);
       stash(flip > 0 ? kStage : 0, 8 * s + 8);
       fetch();
+      __builtin_amdgcn_s_setprio(0);
       __builtin_amdgcn_sched_barrier(0);
     };
     for (int s = s0; s < s1; ++s) {

@@ -29,7 +29,12 @@ template <int NB> struct Waves { static constexpr int qw = NB == 1 ? 4 : NB == 4
 struct Frag {
   double r, i, s;   // re, im, re + im
 };
-__device__ __forceinline__ Frag frag(double2 v) { return Frag{v.x, v.y, v.x + v.y}; }
+template <bool CJ = false> __device__ __forceinline__ Frag frag(double2 v) {
+  return Frag{v.x, v.y, CJ ? v.x - v.y : v.x + v.y};
+}
+// a fragment as stored in LDS, with or without its sum
+__device__ __forceinline__ void put_frag(Frag& d, double2 v) { d = frag(v); }
+__device__ __forceinline__ void put_frag(double2& d, double2 v) { d = v; }
 struct Acc3 {
   d4 p1, p2, p3;
 };
@@ -39,16 +44,19 @@ __device__ __forceinline__ void mma3(const Frag& a, const Frag& b, Acc3& c) {
   c.p2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.i, b.i, c.p2, 0, 0, 0);
   c.p3 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.s, b.s, c.p3, 0, 0, 0);
 }
-__device__ __forceinline__ Frag acc3_frag(const Acc3& c, int r) {
-  const double re = c.p1[r] - c.p2[r], im = c.p3[r] - c.p1[r] - c.p2[r];
-  return Frag{re, im, re + im};
+// CJ: one factor was conjugated, its imaginary part entering with its stored
+// sign, so that p2 counts with the other sign
+template <bool CJ = false> __device__ __forceinline__ Frag acc3_frag(const Acc3& c, int r) {
+  const double re = CJ ? c.p1[r] + c.p2[r] : c.p1[r] - c.p2[r];
+  const double s = __builtin_fma(CJ ? 2.0 : -2.0, c.p2[r], c.p3[r]);
+  return Frag{re, s - re, s};
 }
 
 // Fragments of a small matrix in LDS, zero past nao.  ROWS: lane l of
 // fragment (b, s) holds M[16 b + l % 16][4 s + l / 16] (an A operand),
 // otherwise M[4 s + l / 16][16 b + l % 16] (a B operand); herm: of M^H.
-template <int NB, int KS, bool ROWS>
-__device__ __forceinline__ void lds_fragments(double2* dst, const double2* M, int n, bool herm, int nthreads) {
+template <int NB, int KS, bool ROWS, class F>
+__device__ __forceinline__ void lds_fragments(F* dst, const double2* M, int n, bool herm, int nthreads) {
   for (int e = threadIdx.x; e < NB * KS * 64; e += nthreads) {
     const int l = e & 63, f = e >> 6, b = f / KS, s = f - b * KS;
     const int x = 16 * b + (l & 15), y = 4 * s + (l >> 4);
@@ -58,7 +66,7 @@ __device__ __forceinline__ void lds_fragments(double2* dst, const double2* M, in
       v = M[herm ? c * n + r : r * n + c];
       if (herm) v.y = -v.y;
     }
-    dst[e] = v;
+    put_frag(dst[e], v);
   }
 }
 
@@ -92,6 +100,7 @@ template <int KS>
 __global__ void __launch_bounds__(64 * Waves<(KS + 3) / 4>::n) sand_prod_k(SandProd d) {
   constexpr int NB = (KS + 3) / 4, QW = Waves<NB>::qw, NT = 64 * Waves<NB>::n;
   constexpr bool kWhole = NB <= 2;   // all fragments of the next V_Q fit in registers
+  // (without the sums: forming them cost no more than the longer LDS reads here)
   __shared__ double2 ldsL[NB * KS * 64], ldsR[NB * KS * 64];
   const int n = d.nao, n2 = n * n;
   const SandPos p = sand_pos(d.nt, d.nk, d.naux, d.qlen);
@@ -192,12 +201,16 @@ __global__ void __launch_bounds__(64 * Waves<(KS + 3) / 4>::n) sand_sum_k(SandSu
   constexpr int NB = (KS + 3) / 4, QW = Waves<NB>::qw, NT = 64 * Waves<NB>::n;
   constexpr bool kWhole = NB <= 2;
   constexpr unsigned ES = sizeof(T);
-  constexpr int kRed = QW > 1 ? (QW - 1) * NB * NB * 4 * 64 : 0;
-  __shared__ double2 lds[NB * KS * 64 > kRed ? NB * KS * 64 : kRed];
+  // fragments of G, then (in their place) the sums of the other Q streams
+  constexpr int kFrag = NB * KS * 64 * (int)sizeof(Frag);
+  constexpr int kRed = QW > 1 ? (QW - 1) * NB * NB * 4 * 64 * (int)sizeof(double2) : 0;
+  __shared__ __attribute__((aligned(16))) char lds_raw[kFrag > kRed ? kFrag : kRed];
+  Frag* const ldsG = (Frag*)lds_raw;
+  double2* const lds = (double2*)lds_raw;
   const int n = d.nao, n2 = n * n;
   const SandPos p = sand_pos(d.nt, d.nk, d.naux, d.qlen);
   const int kq = d.tab[p.t * d.tstab + p.k];
-  lds_fragments<NB, KS, true>(lds, d.G + p.t * d.tsG + (long long)(d.tabG ? kq : p.k) * n2, n, d.hermG != 0, NT);
+  lds_fragments<NB, KS, true>(ldsG, d.G + p.t * d.tsG + (long long)(d.tabG ? kq : p.k) * n2, n, d.hermG != 0, NT);
   __syncthreads();
   const int lane = threadIdx.x & 63, r16 = lane & 15, kl = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -220,9 +233,9 @@ __global__ void __launch_bounds__(64 * Waves<(KS + 3) / 4>::n) sand_sum_k(SandSu
   auto ld = [&](__amdgpu_buffer_rsrc_t rs, unsigned v, int s) {
     return to_d2(buf_load<T>(rs, 4 * s + kl < n ? v : kOut, step * (unsigned)s));
   };
-  // conjugations: A^H takes conj(A), B^H takes conj(B)
-  auto fa = [&](double2 v) { return frag(BH ? v : double2{v.x, -v.y}); };
-  auto fb = [&](double2 v) { return frag(BH ? double2{v.x, -v.y} : v); };
+  // conjugations: B^H takes conj(B) in the first product, A^H conj(A) in the second
+  auto fa = [&](double2 v) { return frag<!BH>(v); };
+  auto fb = [&](double2 v) { return frag<BH>(v); };
   double2 a[kWhole ? NB : 1][kWhole ? KS : 1], b[kWhole ? KS : 1];
   auto fetchA = [&](int Q) {
     if constexpr (kWhole) {
@@ -258,7 +271,7 @@ __global__ void __launch_bounds__(64 * Waves<(KS + 3) / 4>::n) sand_sum_k(SandSu
       for (int s = 0; s < KS; ++s) {
         const Frag x = fb(b[s]);
 #pragma unroll
-        for (int i = 0; i < NB; ++i) mma3(frag(lds[(i * KS + s) * 64 + lane]), x, X[i]);
+        for (int i = 0; i < NB; ++i) mma3(ldsG[(i * KS + s) * 64 + lane], x, X[i]);
       }
       fetchB(Qn);
       __builtin_amdgcn_sched_barrier(0);
@@ -272,13 +285,13 @@ __global__ void __launch_bounds__(64 * Waves<(KS + 3) / 4>::n) sand_sum_k(SandSu
         __builtin_amdgcn_sched_barrier(0);
         const Frag x = fb(g[s & 1]);
 #pragma unroll
-        for (int i = 0; i < NB; ++i) mma3(frag(lds[(i * KS + s) * 64 + lane]), x, X[i]);
+        for (int i = 0; i < NB; ++i) mma3(ldsG[(i * KS + s) * 64 + lane], x, X[i]);
       }
     }
     if constexpr (kWhole) {
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
-        const Frag t = acc3_frag(X[s / 4], s % 4);
+        const Frag t = acc3_frag<BH>(X[s / 4], s % 4);
 #pragma unroll
         for (int i = 0; i < NB; ++i) mma3(fa(a[i][s]), t, o[i]);
       }
@@ -296,7 +309,7 @@ __global__ void __launch_bounds__(64 * Waves<(KS + 3) / 4>::n) sand_sum_k(SandSu
           for (int i = 0; i < NB; ++i) g[(s + 1) & 1][i] = ld(rs, voA[i], s + 1);
         }
         __builtin_amdgcn_sched_barrier(0);
-        const Frag t = acc3_frag(X[s / 4], s % 4);
+        const Frag t = acc3_frag<BH>(X[s / 4], s % 4);
 #pragma unroll
         for (int i = 0; i < NB; ++i) mma3(fa(g[s & 1][i]), t, o[i]);
       }
@@ -310,7 +323,7 @@ __global__ void __launch_bounds__(64 * Waves<(KS + 3) / 4>::n) sand_sum_k(SandSu
       for (int i = 0; i < NB; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const Frag v = acc3_frag(o[i], r);
+          const Frag v = acc3_frag<!BH>(o[i], r);
           w[(i * 4 + r) * 64 + lane] = double2{v.r, v.i};
         }
     }
@@ -326,7 +339,7 @@ __global__ void __launch_bounds__(64 * Waves<(KS + 3) / 4>::n) sand_sum_k(SandSu
   for (int i = 0; i < NB; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const Frag v = acc3_frag(o[i], r);
+      const Frag v = acc3_frag<!BH>(o[i], r);
       double re = v.r, im = v.i;
       if constexpr (QW > 1) {
 #pragma unroll
