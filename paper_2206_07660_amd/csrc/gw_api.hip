@@ -365,8 +365,9 @@ struct Count {
 // where the launch has room.  The midpoints and their decisions, and so the
 // result, are those of the plain bisection; where the count is flat (a gap at
 // low temperature) nothing is settled and every midpoint is evaluated.
-// Measured (4x4x4, nao 26, 100 frequencies): 48 counts and 17.3 ms before, 16 counts and 1.9 ms now, with the
-// wave-per-matrix kernel and the counts in pinned memory.
+// Measured (4x4x4, nao 26, 100 frequencies): 48 counts and 17.3 ms before, 16
+// counts and 1.9 ms now, with the wave-per-matrix kernel and the counts in
+// pinned memory.
 struct MuRoot {
   Count f;
   double target, tol, margin;
@@ -385,7 +386,7 @@ struct MuRoot {
   // the same with up to 15 counts per launch, where one costs little more than
   // another: each round takes an even grid of the bracket and points at 1e-2,
   // 1e-4 and 1e-6 of its width around the secant's root (2x2x2, nao 6, 24
-  // frequencies: 22 launches per search before, @@ now)
+  // frequencies, two searches: 23 -> 17 count launches)
   gw_status enclose_wide(double a, double na, double b, double nb) {
     for (int it = 0; it < 12 && nb > na; ++it) {
       const double w = b - a, x = a + w * (target - na) / (nb - na);
@@ -1478,26 +1479,45 @@ static gw_status solve_core(gw_ctx* c, const gw_z* P0, gw_z* Pt, const int* sel,
     const long long span = nmat * nn, all = sel ? (long long)c->nk * c->d.nw_b * nn : span;
     return run(c, g, Ext{-xo, span - xo}, Ext{-yo, (Y == Bm ? all : span) - yo}, Ext{-zo, (Z == Bm ? all : span) - zo});
   };
-  for (int j0 = 0; j0 < n; j0 += kNb) {
-    const int j1 = std::min(j0 + kNb, n), w = j1 - j0, rest = n - j1;
-    if (n - j0 <= 512) {
-      HIPCHK(c, wlu_factor_launch(Am, Bm, sel, n, j0, nmat, c->dflag, c->st));
+  for (int j0 = 0; j0 < n;) {
+    // Two panels per trailing update where both are register-resident: the
+    // update reads and writes all of the trailing A and B and is bound by that
+    // (404 matrices of order 250, with the back substitution by pairs of blocks:
+    // 4.04 -> 3.30 ms)
+    const bool small = n - j0 <= 512, two = small && n - j0 > 2 * kNb;
+    const int j1 = std::min(j0 + (two ? 2 : 1) * kNb, n), w = j1 - j0, rest = n - j1;
+    if (small) {
+      HIPCHK(c, wlu_factor_launch(Am, Bm, sel, n, j0, false, nmat, c->dflag, c->st));
     } else {
       HIPCHK(c, wlu_launch(1, nullptr, Am, Bm, sel, n, j0, kNb, nmat, c->dflag, c->st));
       HIPCHK(c, wlu_launch(2, nullptr, Am, Bm, sel, n, j0, kNb, nmat, c->dflag, c->st));
+    }
+    if (two) {
+      const int jm = j0 + kNb;
+      // the second panel -= L21 U12 of the first
+      if ((s = gemm(Am, (long long)jm * n + j0, Am, (long long)j0 * n + jm, Am, (long long)jm * n + jm, n - jm, kNb,
+                    kNb)) != GW_OK) return s;
+      HIPCHK(c, wlu_factor_launch(Am, Bm, sel, n, jm, true, nmat, c->dflag, c->st));
     }
     // A22 -= L21 U12 ;  B2 -= L21 B1
     if ((s = gemm(Am, (long long)j1 * n + j0, Am, (long long)j0 * n + j1, Am, (long long)j1 * n + j1,
                   rest, rest, w)) != GW_OK) return s;
     if ((s = gemm(Am, (long long)j1 * n + j0, Bm, (long long)j0 * n, Bm, (long long)j1 * n,
                   rest, n, w)) != GW_OK) return s;
+    j0 = j1;
   }
   const int nblk = (n + kNb - 1) / kNb;
-  for (int b = nblk - 1; b >= 0; --b) {
+  // back substitution, two blocks per update of the rows above them
+  for (int b = nblk - 1; b >= 0; b -= 2) {
     const int j0 = b * kNb, w = std::min(kNb, n - j0);
     HIPCHK(c, wlu_back_launch(Am, Bm, sel, n, j0, nmat, c->st));
-    // B[0:j0] -= U[0:j0, j0:j0+w] B[j0:j0+w]
-    if ((s = gemm(Am, (long long)j0, Bm, (long long)j0 * n, Bm, 0, j0, n, w)) != GW_OK) return s;
+    if (b == 0) break;
+    // the block above: B[jm:j0] -= U[jm:j0, j0:j0+w] B[j0:j0+w], then solved
+    const int jm = j0 - kNb;
+    if ((s = gemm(Am, (long long)jm * n + j0, Bm, (long long)j0 * n, Bm, (long long)jm * n, kNb, n, w)) != GW_OK) return s;
+    HIPCHK(c, wlu_back_launch(Am, Bm, sel, n, jm, nmat, c->st));
+    // B[0:jm] -= U[0:jm, jm:j0+w] B[jm:j0+w]
+    if ((s = gemm(Am, (long long)jm, Bm, (long long)jm * n, Bm, 0, jm, n, kNb + w)) != GW_OK) return s;
   }
   const double nd = n;
   if ((s = prof_end(c, KC_WDYSON, e0, (32.0 / 3.0) * nd * nd * nd * nmat)) != GW_OK) return s;

@@ -268,8 +268,9 @@ hipError_t sxs_add_launch(const double2* S, const double2* X, double2* Out, int 
 // interchanges and L11^{-1} on the columns right of it and on B; wlu_back_launch
 // applies U11^{-1} to the panel's rows of B.  wlu_launch: 0 sets A = I - P0 and
 // B = P0; 1 and 2 are the panel and its triangular solve for more rows.
-hipError_t wlu_factor_launch(double2* A, double2* B, const int* sel, int n, int j0, long long nmat, int* flag,
-                             hipStream_t st);
+// (second: the panel before has been applied to this panel only, see gw_wlu.hip)
+hipError_t wlu_factor_launch(double2* A, double2* B, const int* sel, int n, int j0, bool second, long long nmat,
+                             int* flag, hipStream_t st);
 hipError_t wlu_back_launch(const double2* A, double2* B, const int* sel, int n, int j0, long long nmat, hipStream_t st);
 hipError_t wlu_launch(int which, const double2* P0, double2* A, double2* B, const int* sel, int n, int j0, int nb,
                       long long nmat, int* flag, hipStream_t st);

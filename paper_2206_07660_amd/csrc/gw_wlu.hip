@@ -11,7 +11,8 @@
 // registers, so that the other columns are read and written once.
 // Before, panel steps and triangular rows each went through global memory with
 // a barrier per level of the search: for 404 matrices of order 250 (ms, all
-// panels) 1.53 + 2.36 and 1.27 (back substitution) against 0.80 and 0.26.
+// panels) 1.53 + 2.36 and 1.27 (back substitution) against 0.99 and 0.25; two
+// panels per trailing update save 0.9 ms of its 2.8.
 #include <hip/hip_runtime.h>
 
 #include "gw_device.h"
@@ -50,14 +51,17 @@ __device__ __forceinline__ unsigned wave_max(unsigned x) {
 
 // Factors columns j0 .. j0+31 of A (rows j0 .. n-1, at most NT of them), then
 // applies the interchanges and L11^{-1} to the columns right of the panel and
-// to all columns of B.  The pivot is the largest remaining |re| + |im| of the
+// to all columns of B.  second: the panel before (columns j0-32 ..) has not
+// been applied to those columns yet, only to this panel; its part enters here,
+// row by row of its U12, and its L rows take part in the interchanges, so that
+// one update of 64 columns follows both panels.  The pivot is the largest remaining |re| + |im| of the
 // column to 2^-10, the uppermost row among equals.
-template <int NT>
+template <int NT, bool second>
 __global__ void __launch_bounds__(NT) wlu_factor_k(double2* A, double2* B, const int* sel, int n, int j0, int* flag) {
   constexpr int NW = NT / 64;
   __shared__ double2 cand[2][NW][kNb];
   __shared__ unsigned keys[2][NW];
-  __shared__ double2 L[kNb][kNb + 1];
+  __shared__ double2 L[kNb][kNb + 1], Lp[second ? kNb : 1][kNb + 1];
   __shared__ int src[kNb], dpos[kNb], dsrc[kNb], nd_s;
   const size_t nn = (size_t)n * n;
   double2* Am = A + blockIdx.x * nn;
@@ -136,9 +140,18 @@ __global__ void __launch_bounds__(NT) wlu_factor_k(double2* A, double2* B, const
     }
   }
   __syncthreads();
-  const int nd = nd_s, right = n - j0 - w;
-  for (int e = tid; e < right + n; e += NT) {
-    double2* M = (e < right ? Am + (j0 + w + e) : Bm + (e - right)) + (size_t)j0 * n;
+  const int nd = nd_s, right = n - j0 - w, left = second ? kNb : 0;
+  if constexpr (second) {
+    // L of the panel before in this panel's rows, in their final order
+    for (int e = tid; e < kNb * kNb; e += NT) {
+      const int i = e / kNb, t = e - i * kNb;
+      Lp[i][t] = i < w ? Am[(size_t)(j0 + src[i]) * n + j0 - kNb + t] : double2{0.0, 0.0};
+    }
+    __syncthreads();
+  }
+  for (int e = tid; e < left + right + n; e += NT) {
+    const int er = e - left;
+    double2* M = (er < 0 ? Am + (j0 + er) : er < right ? Am + (j0 + w + er) : Bm + (er - right)) + (size_t)j0 * n;
 #pragma unroll
     for (int i = 0; i < kNb; ++i) x[i] = i < w ? M[(size_t)src[i] * n] : double2{0.0, 0.0};
     for (int d = 0; d < nd; d += 8) {
@@ -149,9 +162,26 @@ __global__ void __launch_bounds__(NT) wlu_factor_k(double2* A, double2* B, const
       for (int i = 0; i < 8; ++i)
         if (d + i < nd) M[(size_t)dpos[d + i] * n] = z[i];
     }
+    if (second && er >= 0) {
+      const double2* u = M - (size_t)kNb * n;
+      double2 y[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) y[t] = u[(size_t)t * n];
+#pragma unroll
+      for (int t = 0; t < kNb; ++t) {
+        const double2 yt = y[t % 4];
+        if (t + 4 < kNb) y[t % 4] = u[(size_t)(t + 4) * n];
+#pragma unroll
+        for (int i = 0; i < kNb; ++i) {
+          if constexpr (second) x[i] = cfnma(Lp[i][t], yt, x[i]);
+          if (i % 8 == 7) __builtin_amdgcn_sched_barrier(0);   // eight entries of L in flight
+        }
+      }
+    }
+    const int ws = second && er < 0 ? 0 : w;   // the panel before is only interchanged
 #pragma unroll
     for (int t = 0; t < kNb - 1; ++t)
-      if (t + 1 < w) {
+      if (t + 1 < ws) {
 #pragma unroll
         for (int i = t + 1; i < kNb; ++i) x[i] = cfnma(L[i][t], x[t], x[i]);
         __builtin_amdgcn_sched_barrier(0);   // L is read as it is used, not ahead into registers
@@ -196,12 +226,18 @@ __global__ void __launch_bounds__(256) wlu_back_k(const double2* A, double2* B, 
   }
 }
 
-hipError_t wlu_factor_launch(double2* A, double2* B, const int* sel, int n, int j0, long long nmat, int* flag,
-                             hipStream_t st) {
+hipError_t wlu_factor_launch(double2* A, double2* B, const int* sel, int n, int j0, bool second, long long nmat,
+                             int* flag, hipStream_t st) {
   if (nmat <= 0) return hipSuccess;
   if (n - j0 > 512) return hipErrorInvalidValue;
-  if (n - j0 <= 256) wlu_factor_k<256><<<(unsigned)nmat, 256, 0, st>>>(A, B, sel, n, j0, flag);
-  else wlu_factor_k<512><<<(unsigned)nmat, 512, 0, st>>>(A, B, sel, n, j0, flag);
+  const unsigned g = (unsigned)nmat;
+  if (n - j0 <= 256) {
+    if (second) wlu_factor_k<256, true><<<g, 256, 0, st>>>(A, B, sel, n, j0, flag);
+    else wlu_factor_k<256, false><<<g, 256, 0, st>>>(A, B, sel, n, j0, flag);
+  } else {
+    if (second) wlu_factor_k<512, true><<<g, 512, 0, st>>>(A, B, sel, n, j0, flag);
+    else wlu_factor_k<512, false><<<g, 512, 0, st>>>(A, B, sel, n, j0, flag);
+  }
   return hipGetLastError();
 }
 
