@@ -24,10 +24,9 @@ import os
 import sys
 
 COPY_BYTES = 4 << 30
-# kernel-name prefixes (tile shape and class tag of zgemm_k) of the launches bench.py times
-CLASSES = {"pol_contract": "zgemm_k<2, 2, 1, 2, 2, 1,", "se_contract": "zgemm_k<2, 2, 1, 2, 3, 3,",
-           "pol_producer": "zgemm_k<2, 2, 1, 2, 4, 2,", "se_producer": "zgemm_k<2, 2, 1, 2, 4, 4,",
-           "se_final": "zgemm_k<1, 1, 4, 2, 2, 5,",
+# kernel-name prefixes (zgemm_k: tile shape and class tag) of the launches bench.py times
+CLASSES = {"pol_contract": "pol_acc_k<", "se_contract": "zgemm_k<2, 2, 1, 2, 3, 3,",
+           "pol_producer": "sand_prod_k<", "se_final": "sand_sum_k<",
            # split-bf16 contractions of the GW_PREC_BF16X3 path
            "pol_contract_bf16x3": "bsgemm_k<2, 2, 2, 2, 1,", "se_contract_bf16x3": "bsgemm_k<2, 4, 4, 2, 3,"}
 
