@@ -42,10 +42,11 @@
  * Environment (read by gw_create).  GW_DEBUG_BOUNDS=1 makes every call check
  *   on the host, before launching, that each GEMM descriptor it builds stays
  *   inside the extents of its operands (a failed check returns GW_ERR_ARG);
- *   GW_TILE_CFG=0..9 forces the tile shape of the two large fp64
+ *   GW_TILE_CFG=0..10 forces the tile shape of the two large fp64
  *   contractions (measurement only): 0..4 the four-product complex MFMA form,
- *   5..9 the three-product (Gauss) form (defaults: 0 for the polarization,
- *   7 for the self-energy); the Hermitian polarization needs a square shape:
+ *   5..10 the three-product (Gauss) form (by default the polarization runs by
+ *   16 x 16 blocks, the self-energy on 7, or on 10 where a 64-row tile would
+ *   be at most half full); the Hermitian polarization needs a square shape:
  *   0, 4 or 5.  GW_PROD_TILES=1 runs the fp32 producers on the tiled GEMM
  *   instead of the streaming kernel.  GW_SPLIT_CFG selects split-bf16 tiles:
  *   bf16x3 self-energy 0 = 128x128 (default), 1 = 64x64, 2 = 128x64; bf16x6
@@ -223,7 +224,9 @@ gw_status gw_set_workspace(gw_ctx* ctx, void* dev, size_t bytes, int tau_chunk);
  * tau), sign chosen so that the static bubble is negative semidefinite):
  *   P0^q_{QQ'}(tau_i) = -(ns/Nk) sum_k sum_{abcd} V^{k,k+q}_{da}(Q) G^{k+q}_{ab}(tau_i)
  *                       V^{k+q,k}_{bc}(Q') G^k_{cd}(tau_{ntau-1-i})
- * for q = q0 .. q0+nq-1, written to P0_tau[q-q0][i] (overwritten).          */
+ * for q = q0 .. q0+nq-1, written to P0_tau[q-q0][i] (overwritten).  In fp64 a
+ * range that holds both q and -q contracts one of them: the pair relation of V
+ * gives P0^{-q}(beta - tau) = P0^q(tau)^T for any G.                        */
 gw_status gw_polarization(gw_ctx* ctx, const void* V, const gw_z* G_tau, int q0, int nq,
                           gw_z* P0_tau);   /* V: gw_z (GW_PREC_FP64) or gw_c (the other modes) */
 

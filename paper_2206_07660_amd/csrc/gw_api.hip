@@ -372,10 +372,18 @@ struct MuRoot {
   Count f;
   double target, tol, margin;
   double sure_lo = -HUGE_VAL, sure_hi = HUGE_VAL;   // N_e < target up to here / > target from here
+  bool rising = true;                               // no two counts so far contradict that
 
   void learn(double mu, double n) {
+    if (!rising) return;
     if (n < target - margin) sure_lo = std::max(sure_lo, mu);
     if (n > target + margin) sure_hi = std::min(sure_hi, mu);
+    if (sure_lo >= sure_hi) {
+      // not a count that rises with mu (a coarse basis): settle nothing
+      rising = false;
+      sure_lo = -HUGE_VAL;
+      sure_hi = HUGE_VAL;
+    }
   }
   gw_status eval(const double* mu, int n, double* ne) {
     const gw_status s = f.at(mu, n, ne);
