@@ -15,6 +15,7 @@
 #include "../../include/gw.h"
 #include "grids.h"
 #include "gw_kernels.h"
+#include "gw_mu.h"
 #include "ir.h"
 
 // Fixed scratch for gw_polarization_noalloc: a file-scope device array, one
@@ -612,9 +613,7 @@ gw_status gw_create(const gw_dims* d, void* hip_stream, gw_ctx** out) {
     const char* gg = std::getenv("GW_SPLIT_GROUP");
     c->split_group = gg ? std::atoi(gg) : 0;
   }
-  // several mu per electron-count launch while their matrices (one wave each)
-  // leave the chip's 8192 wave slots half empty
-  c->nmu = (int)std::max(1LL, std::min(15LL, 4096LL / ((long long)d->nw_f * c->nk)));
+  c->nmu = mu_batch(d->nao, (long long)d->nw_f * c->nk);
   if (upload(c, &c->dplus, plus.data(), plus.size() * sizeof(int)) != GW_OK ||
       upload(c, &c->dminus, minus.data(), minus.size() * sizeof(int)) != GW_OK ||
       hipMalloc((void**)&c->dflag, sizeof(int)) != hipSuccess ||
