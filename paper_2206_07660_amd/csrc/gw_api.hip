@@ -311,17 +311,11 @@ gw_status read_flag(gw_ctx* c, const char* what) {
   return GW_OK;
 }
 
-// Dyson matrices at nmu values of mu: nao <= 32 on the wave-per-matrix kernel.
+// Dyson matrices at nmu values of mu: nao <= 32 on the wave-per-matrix kernel,
+// larger ones (nmu = 1, see mu_batch) a workgroup each.
 hipError_t dyson_any(gw_ctx* c, const DysonArgs& a, int nmu) {
   if (c->d.nao <= 32) return dyson_reg_launch(a, c->d.nw_f, nmu, c->st);
-  for (int i = 0; i < nmu; ++i) {
-    DysonArgs b = a;
-    if (i > 0) b.mu = a.more[i - 1];
-    if (a.part) b.part = a.part + (size_t)i * c->d.nw_f * c->nk;
-    const hipError_t e = dyson_launch(b, c->d.nw_f, c->st);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return nmu == 1 ? dyson_launch(a, c->d.nw_f, c->st) : hipErrorInvalidValue;
 }
 
 // The electron count as a function of mu, for one set of Dyson inputs.
@@ -329,7 +323,8 @@ struct Count {
   gw_ctx* c;
   const gw_z *H0, *S, *Sinf, *Siw;
 
-  // counts at n <= c->nmu values in one launch (G written for n = 1, if given)
+  // counts at n <= c->nmu values in one launch (G written for n = 1, if given),
+  // with a zero pivot left to count_status or to the flag
   gw_status at(const double* mu, int n, double* ne, gw_z* Gout = nullptr) const {
     DysonArgs a{};
     a.H0 = (const double2*)H0;
@@ -349,199 +344,16 @@ struct Count {
     // the sums go to pinned host memory: no copy to wait for
     HIPCHK(c, sum_rows_launch(c->dcnt, c->d.nw_f * c->nk, n, -(double)c->d.ns / c->nk, c->hcnt, c->st));
     HIPCHK(c, hipStreamSynchronize(c->st));
-    for (int i = 0; i < n; ++i) {
-      ne[i] = c->hcnt[i];
-      if (!std::isfinite(ne[i])) return fail(c, GW_ERR_NONFINITE, "electron count is not finite");
-    }
+    for (int i = 0; i < n; ++i) ne[i] = c->hcnt[i];
     return GW_OK;
   }
-};
-
-// Root of N_e(mu) = target by bracket expansion from mu0 +- 1 Ha and bisection
-// to a bracket of tol.  N_e does not decrease with mu, so a count that differs
-// from the target by more than its rounding (margin) settles every midpoint on
-// its side: a fast bracketing search (Chandrupatla, Adv. Eng. Software 28
-// (1997) 145) encloses the root first, and the bisection evaluates only the
-// midpoints inside that enclosure, all those of its next levels in one launch
-// where the launch has room.  The midpoints and their decisions, and so the
-// result, are those of the plain bisection; where the count is flat (a gap at
-// low temperature) nothing is settled and every midpoint is evaluated.
-// Measured (4x4x4, nao 26, 100 frequencies): 48 counts and 17.3 ms before, 16
-// counts and 1.9 ms now, with the wave-per-matrix kernel and the counts in
-// pinned memory.
-struct MuRoot {
-  Count f;
-  double target, tol, margin;
-  double sure_lo = -HUGE_VAL, sure_hi = HUGE_VAL;   // N_e < target up to here / > target from here
-  bool rising = true;                               // no two counts so far contradict that
-
-  void learn(double mu, double n) {
-    if (!rising) return;
-    if (n < target - margin) sure_lo = std::max(sure_lo, mu);
-    if (n > target + margin) sure_hi = std::min(sure_hi, mu);
-    if (sure_lo >= sure_hi) {
-      // not a count that rises with mu (a coarse basis): settle nothing
-      rising = false;
-      sure_lo = -HUGE_VAL;
-      sure_hi = HUGE_VAL;
-    }
-  }
-  gw_status eval(const double* mu, int n, double* ne) {
-    const gw_status s = f.at(mu, n, ne);
-    if (s == GW_OK)
-      for (int i = 0; i < n; ++i) learn(mu[i], ne[i]);
+  gw_status operator()(const double* mu, int n, double* ne) const { return at(mu, n, ne); }
+  // one count that has to be finite
+  gw_status one(double mu, double* n, gw_z* Gout = nullptr) const {
+    const char* why = "";
+    gw_status s = at(&mu, 1, n, Gout);
+    if (s == GW_OK && (s = count_status(*n, &why)) != GW_OK) return fail(c, s, why);
     return s;
-  }
-  // the same with up to 15 counts per launch, where one costs little more than
-  // another: each round takes an even grid of the bracket and points at 1e-2,
-  // 1e-4 and 1e-6 of its width around the secant's root (2x2x2, nao 6, 24
-  // frequencies, two searches: 23 -> 17 count launches)
-  gw_status enclose_wide(double a, double na, double b, double nb) {
-    for (int it = 0; it < 12 && nb > na; ++it) {
-      const double w = b - a, x = a + w * (target - na) / (nb - na);
-      if (w <= 16.0 * tol || (sure_lo >= a && sure_hi <= b && w <= 64.0 * tol)) break;
-      double mu[15], ne[15];
-      int n = 0;
-      for (int i = 1; i <= 7; ++i) mu[n++] = a + w * i / 8.0;
-      for (double r : {1e-2, 1e-4, 1e-6}) {
-        const double d = std::max(r * w, 8.0 * tol);
-        mu[n++] = x - d;
-        mu[n++] = x + d;
-      }
-      mu[n++] = x;
-      std::sort(mu, mu + n);
-      const gw_status s = eval(mu, n, ne);
-      if (s != GW_OK) return s;
-      // the counts next to the root that stand clear of their rounding
-      const double a0 = a, b0 = b;
-      for (int i = 0; i < n; ++i) {
-        if (!(mu[i] > a0 && mu[i] < b0)) continue;
-        if (ne[i] < target - margin && mu[i] > a) { a = mu[i]; na = ne[i]; }
-      }
-      for (int i = n - 1; i >= 0; --i) {
-        if (!(mu[i] > a0 && mu[i] < b0)) continue;
-        if (ne[i] > target + margin && mu[i] < b) { b = mu[i]; nb = ne[i]; }
-      }
-      if (!(b - a < 0.9 * w)) break;          // flat, or as narrow as the rounding allows
-    }
-    return GW_OK;
-  }
-
-  // narrows [a, b] (counts na <= target <= nb) and settles both sides of the root
-  gw_status enclose(double a, double na, double b, double nb) {
-    gw_status s;
-    double x1 = b, f1 = nb - target, x2 = a, f2 = na - target, x3 = a, f3 = f2, t = 0.5, slope = 0.0, best = 0.5 * (a + b);
-    for (int it = 0; it < 40 && f1 * f2 < 0.0; ++it) {
-      const double x = x1 + t * (x2 - x1);
-      double n = 0.0;
-      if ((s = eval(&x, 1, &n)) != GW_OK) return s;
-      const double fx = n - target;
-      slope = std::fabs((fx - f1) / (x - x1));
-      if ((fx < 0.0) == (f1 < 0.0)) {
-        x3 = x1; f3 = f1;
-      } else {
-        x3 = x2; f3 = f2;
-        x2 = x1; f2 = f1;
-      }
-      x1 = x; f1 = fx;
-      best = std::fabs(f1) < std::fabs(f2) ? x1 : x2;
-      const double width = std::fabs(x1 - x2);
-      if (std::min(std::fabs(f1), std::fabs(f2)) <= margin || width <= 16.0 * tol) break;
-      const double xi = (x1 - x2) / (x3 - x2), ph = (f1 - f2) / (f3 - f2);
-      t = 0.5;
-      if (ph * ph < xi && (1.0 - ph) * (1.0 - ph) < 1.0 - xi)
-        t = f1 / (f2 - f1) * f3 / (f2 - f3) + (x3 - x1) / (x2 - x1) * f1 / (f3 - f1) * f2 / (f3 - f2);
-      const double tl = std::min(0.5, 8.0 * tol / width);
-      t = std::min(1.0 - tl, std::max(tl, t));
-    }
-    if (!(slope > 0.0) || !std::isfinite(slope)) return GW_OK;
-    // two points just outside the rounding of the count
-    double d = std::max(4.0 * margin / slope, 4.0 * tol);
-    for (int it = 0; it < 3; ++it, d *= 8.0) {
-      double mu[2], n[2];
-      int k = 0;
-      if (best - d > sure_lo && best - d > a) mu[k++] = best - d;
-      if (best + d < sure_hi && best + d < b) mu[k++] = best + d;
-      if (k == 0) break;
-      for (int i = 0; i < k; i += f.c->nmu)
-        if ((s = eval(mu + i, std::min(f.c->nmu, k - i), n + i)) != GW_OK) return s;
-      if (sure_lo >= best - d && sure_hi <= best + d) break;
-    }
-    return GW_OK;
-  }
-
-  gw_status find(double mu0, double* out) {
-    gw_ctx* c = f.c;
-    margin = 5e-14 * std::max(1.0, (double)c->d.ns * c->d.nao);
-    gw_status s;
-    double lo = mu0 - 1.0, hi = mu0 + 1.0, step = 1.0, nlo = 0.0, nhi = 0.0;
-    int it = 0;
-    if (c->nmu >= 2) {
-      const double mu[2] = {lo, hi};
-      double n[2];
-      if ((s = eval(mu, 2, n)) != GW_OK) return s;
-      nlo = n[0];
-      nhi = n[1];
-    } else {
-      if ((s = eval(&lo, 1, &nlo)) != GW_OK) return s;
-      if ((s = eval(&hi, 1, &nhi)) != GW_OK) return s;
-    }
-    while (nlo > target) {
-      step *= 2.0;
-      lo -= step;
-      if (++it > 60) return fail(c, GW_ERR_NOCONV, "mu search: no lower bracket");
-      if ((s = eval(&lo, 1, &nlo)) != GW_OK) return s;
-    }
-    step = 1.0;
-    it = 0;
-    while (nhi < target) {
-      step *= 2.0;
-      hi += step;
-      if (++it > 60) return fail(c, GW_ERR_NOCONV, "mu search: no upper bracket");
-      if ((s = eval(&hi, 1, &nhi)) != GW_OK) return s;
-    }
-    if (hi - lo > 64.0 * tol) {
-      s = c->nmu >= 15 ? enclose_wide(lo, nlo, hi, nhi) : enclose(lo, nlo, hi, nhi);
-      if (s != GW_OK) return s;
-    }
-    it = 0;
-    while (hi - lo > tol && it < 400) {
-      // midpoints of the next levels that nothing settles, in one launch
-      double mu[16], ne[16];
-      int n = 0;
-      struct { double lo, hi; } node[31];
-      node[0] = {lo, hi};
-      int cnt = 1;
-      for (int i = 0; i < cnt && n < c->nmu; ++i) {
-        const double l = node[i].lo, h = node[i].hi, mid = 0.5 * (l + h);
-        if (!(h - l > tol)) continue;
-        const bool below = mid <= sure_lo, above = mid >= sure_hi;
-        if (!below && !above) mu[n++] = mid;
-        if (cnt < 31 && !above) node[cnt++] = {mid, h};
-        if (cnt < 31 && !below) node[cnt++] = {l, mid};
-      }
-      if (n > 0 && (s = f.at(mu, n, ne)) != GW_OK) return s;
-      // walk the bisection as far as the evaluated midpoints reach
-      bool moved = true;
-      while (moved && hi - lo > tol && it < 400) {
-        const double mid = 0.5 * (lo + hi);
-        moved = false;
-        int low = -1;
-        if (mid <= sure_lo) low = 1;
-        else if (mid >= sure_hi) low = 0;
-        else
-          for (int i = 0; i < n; ++i)
-            if (mu[i] == mid) low = ne[i] < target;
-        if (low < 0) break;
-        if (low) lo = mid; else hi = mid;
-        moved = true;
-        ++it;
-      }
-      for (int i = 0; i < n; ++i) learn(mu[i], ne[i]);
-    }
-    if (hi - lo > tol) return fail(c, GW_ERR_NOCONV, "mu search: bracket not narrowed to tol");
-    *out = 0.5 * (lo + hi);
-    return GW_OK;
   }
 };
 
@@ -1864,12 +1676,16 @@ gw_status gw_find_mu(gw_ctx* c, const gw_z* H0, const gw_z* S, const gw_z* Sinf,
   double n = 0.0;
   gw_status s;
   const Count count{c, H0, S, Sinf, Siw};
-  auto root = [&](double target, double* out) { return MuRoot{count, target, tol, 0.0}.find(mu0, out); };
+  auto root = [&](double target, double* out) {
+    MuRoot<Count> r{count, c->nmu, target, tol};
+    const gw_status e = r.find(mu0, out);
+    return e == GW_OK || !*r.why ? e : fail(c, e, r.why);
+  };
   double mu = 0.0;
   if (c->mu_window > 0.0) {
     const double w = std::min(c->mu_window, 0.5 * std::min(n_target, (double)c->d.ns * c->d.nao - n_target));
     // keep mu0 when its count is inside the window, else the window's midpoint
-    if ((s = count.at(&mu0, 1, &n)) != GW_OK) return s;
+    if ((s = count.one(mu0, &n)) != GW_OK) return s;
     if (std::fabs(n - n_target) <= w) {
       mu = mu0;
     } else {
@@ -1881,7 +1697,7 @@ gw_status gw_find_mu(gw_ctx* c, const gw_z* H0, const gw_z* S, const gw_z* Sinf,
   } else {
     if ((s = root(n_target, &mu)) != GW_OK) return s;
   }
-  if ((s = count.at(&mu, 1, &n, G_iw)) != GW_OK) return s;
+  if ((s = count.one(mu, &n, G_iw)) != GW_OK) return s;
   if ((s = read_flag(c, "find_mu")) != GW_OK) return s;
   *mu_inout = mu;
   if (n_out) *n_out = n;

@@ -81,7 +81,7 @@ __global__ void __launch_bounds__(256) dyson_reg_k(DysonArgs a, int nw, int tota
       }
     }
   }
-  bool open = r < n, bad = false;            // open: the row has not been a pivot
+  bool open = r < n, bad = false, zero = false;   // open: the row has not been a pivot
   int mycol = 0;                             // the step whose pivot this row was
 #pragma unroll
   for (int i = 0; i < NC; ++i)
@@ -96,7 +96,9 @@ __global__ void __launch_bounds__(256) dyson_reg_k(DysonArgs a, int nw, int tota
       const unsigned key = open ? (hi & ~63u) | (unsigned)(63 - r) : 0u;
       const int p = 63 - (int)(__builtin_amdgcn_readfirstlane(group_max<R>(key)) & 63u);
       const double2 fp{readlane_d(f.x, p), readlane_d(f.y, p)};
-      if (!(fabs(fp.x) + fabs(fp.y) > 0.0)) bad = true;
+      const double fa = fabs(fp.x) + fabs(fp.y);
+      if (!(fa > 0.0)) bad = true;
+      if (fa == 0.0) zero = true;
       const double den = fp.x * fp.x + fp.y * fp.y;
       const double inv = den > 0.0 ? 1.0 / den : 0.0;
       const double2 pinv{fp.x * inv, -fp.y * inv};
@@ -129,7 +131,9 @@ __global__ void __launch_bounds__(256) dyson_reg_k(DysonArgs a, int nw, int tota
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
     }
-  if (bad && lane == 0) atomicOr(a.flag, 1);
+  // a count's zero pivot makes the count infinite: those of a launch may have
+  // been asked for in vain
+  if (bad && lane == 0 && !a.part) atomicOr(a.flag, 1);
   // row r holds row mycol of the transposed inverse, its entry c the column perm[c]
   if (a.logdet) {
     double l = lane < n ? 0.5 * log(dens[lane]) : 0.0;
@@ -157,7 +161,7 @@ __global__ void __launch_bounds__(256) dyson_reg_k(DysonArgs a, int nw, int tota
     }
     if (lane == 0) {
       const double2 rr = a.rrow[iw];
-      a.part[mat] = rr.x * tr - rr.y * ti;
+      a.part[mat] = rr.x * tr - rr.y * ti + (zero ? (double)INFINITY : 0.0);
     }
   }
 }

@@ -216,8 +216,8 @@ bool zgemm_three_product(const GemmDesc& d);
 hipError_t bsgemm_launch(const SplitDesc& d, hipStream_t st);
 hipError_t dyson_launch(const DysonArgs& a, int nw, hipStream_t st);
 // The same for nao <= 32, one wave per matrix; nmu values of mu (a.mu, then
-// a.more) with part[(i * nw + n) * nk + k]; G and logdet of the first one only
-// (nmu = 1).
+// a.more) with part[(i * nw + n) * nk + k], infinite for a zero pivot (which sets
+// the flag without part); G and logdet of the first one only (nmu = 1).
 hipError_t dyson_reg_launch(const DysonArgs& a, int nw, int nmu, hipStream_t st);
 // out[b] = scale * (x[b n] + ... + x[b n + n - 1]) for b < rows
 hipError_t sum_rows_launch(const double* x, int n, int rows, double scale, double* out, hipStream_t st);

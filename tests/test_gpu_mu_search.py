@@ -48,3 +48,75 @@ def test_forms(nao, nk, ntau, gap):
         assert abs(mu2 - mu) < 1e-9
     finally:
         ctx.close()
+
+
+# 48, 960 and 4320 matrices: 15, 4 and 1 values of mu per launch
+@pytest.mark.parametrize("mesh", [(2, 1, 1), (40, 1, 1), (12, 15, 1)])
+@pytest.mark.parametrize("seed,mu0", [(8, 0.0), (32, 0.1), (39, 0.0)])
+def test_count_that_falls(mesh, seed, mu0):
+    """24 nodes at beta 1000: in the gap the count of the sparse grids is not
+    monotonic in mu, and which of its roots is the answer depends on the
+    midpoints that the bisection visits."""
+    from paper_2206_07660_amd import gw
+    beta, ntau, nao = 1000.0, 24, 8
+    rng = np.random.default_rng([seed, 2])
+    e = np.where(np.arange(nao) < 4, -0.6, 0.6) + 0.3 * rng.uniform(-1, 1, (2, nao))
+    g = og.Grids(beta, ntau)
+    r = np.asarray(g.w) @ g.TFp
+
+    def excess(mu):
+        return -np.real(r * (1.0 / (1j * g.wF[:, None, None] + mu - e)).sum((1, 2))).sum() - 8.0
+
+    lo, hi = mu0 - 1.0, mu0 + 1.0
+    assert excess(lo) < 0 < excess(hi)
+    while hi - lo > 1e-13:
+        mid = 0.5 * (lo + hi)
+        x = excess(mid)
+        # the decisions are clear of the counts' rounding, some 1e-12
+        assert hi - lo < 1e-7 or abs(x) > 1e-8
+        lo, hi = (mid, hi) if x < 0 else (lo, mid)
+    ctx = gw.Context(mesh, nao, 4, ntau, beta)
+    try:
+        H0 = np.zeros((ctx.nk, nao, nao), complex)
+        H0[:, np.arange(nao), np.arange(nao)] = np.tile(e, (ctx.nk // 2, 1))
+        S = np.tile(np.eye(nao, dtype=complex), (ctx.nk, 1, 1))
+        mu, _ = gw.gw_find_mu(ctx, dev(H0), dev(S), None, None, 8.0, mu0)
+        # the count rises by more than 10 per Ha at the root
+        assert abs(mu - 0.5 * (lo + hi)) < 1e-8
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("pole,needed", [(0.0, True), (0.5, True), (0.75, False), (-0.75, False)])
+def test_zero_pivot(pole, needed):
+    """A matrix that is singular at one value of mu: an error where the
+    bisection asks for that count, and none where it is only looked at ahead."""
+    from paper_2206_07660_amd import gw
+    beta, ntau, nao, at = 20.0, 20, 3, 10
+    g = og.Grids(beta, ntau)
+    r = np.asarray(g.w) @ g.TFp
+    ctx = gw.Context((1, 1, 1), nao, 4, ntau, beta)
+    try:
+        # diag(i w + mu - 0.4, i w + mu + 0.3, i w + mu - pole), the last one mu - pole at one frequency
+        w = (2.0 * ctx.grids["nF"] + 1.0) * np.pi / beta
+        sig = np.zeros((len(w), 1, nao, nao), complex)
+        sig[at, 0, 2, 2] = 1j * w[at]
+        e = np.array([0.4, -0.3, pole])
+        x = 1j * w[:, None] - e - sig[:, 0, np.arange(3), np.arange(3)]
+        lo, hi, asked = -1.0, 1.0, False
+        while hi - lo > 1e-13 and not asked:
+            mid = 0.5 * (lo + hi)
+            asked = mid == pole
+            if not asked:
+                lo, hi = (mid, hi) if -2.0 * np.real(r[:, None] / (x + mid)).sum() < 2.5 else (lo, mid)
+        assert asked == needed
+        a = (dev(np.diag(e).astype(complex)[None]), dev(np.eye(nao, dtype=complex)[None]), None, dev(sig), 2.5, 0.0)
+        if needed:
+            with pytest.raises(gw.GwError) as err:
+                gw.gw_find_mu(ctx, *a)
+            assert err.value.status == gw.GW_ERR_SINGULAR
+        else:
+            # the count rises by seven per Ha there
+            assert abs(gw.gw_find_mu(ctx, *a)[0] - 0.5 * (lo + hi)) < 1e-10
+    finally:
+        ctx.close()
