@@ -259,6 +259,15 @@ gw_status gw_polarization_noalloc(gw_ctx* ctx, const void* V, const gw_z* G_tau,
  * each two-slot term) is Hermitian: only the output tiles on and above the
  * diagonal are contracted and the rest is filled by conjugation (also when
  * accumulating, where the previous contents must be Hermitian as well).
+ * The whole-chain calls make the same statement of the G that they form a
+ * polarization from: gw_sigma and (with Pt_tau and Pt_iw NULL) gw_sigma_jvp
+ * and gw_sigma_vjp of their G with GW_HERM_FORWARD, gw_sigma_jvp of G and dG
+ * with GW_HERM_TWO_SLOT.  In fp64, with bosonic tables that keep the symmetries
+ * of the exact transforms (those of gw_build_grids do), P~ of a Hermitian G has
+ * P~^q(-i Omega) = P~^q(i Omega)^H, P~^{-q}(i Omega) = conj(P~^q(i Omega)) and
+ * P~^{-q}(beta - tau) = P~^q(tau)^T, and gw_sigma, gw_sigma_jvp (both bits) and
+ * the rebuilt P~ of gw_sigma_vjp compute one q of each pair {q, -q} and take
+ * the other from it.
  * Results for inputs that break these properties are undefined.          */
 enum { GW_HERM_FORWARD = 1, GW_HERM_TWO_SLOT = 2 };
 gw_status gw_set_hermitian(gw_ctx* ctx, int mode);
@@ -496,7 +505,9 @@ gw_status gw_dyson_jvp(gw_ctx* ctx, const gw_z* S, const gw_z* G_iw, const gw_z*
  * for all q as gw_sigma leaves them; with both NULL, P~^q is rebuilt q by q
  * inside the call from G (one polarization, transform and solve per q, with
  * the Hermitian mode of gw_set_hermitian), so nothing of size Nk naux^2 is
- * held.  The JVP uses GW_HERM_TWO_SLOT when set (dG Hermitian like G).
+ * held.  The JVP uses GW_HERM_TWO_SLOT when set (dG Hermitian like G); with
+ * GW_HERM_FORWARD too it reads a given P~ at one q of each pair {q, -q}.  The
+ * VJP reads a given P~ at every q and holds for any G then.
  * Outputs are overwritten: dSig_inf [k][i][j], dSig_tau and G_bar
  * [tau][k][i][j].  Workspace GW_OP_SIGMA.  Both run in every precision
  * (V complex128 or, in the complex64 modes, gw_c).                         */

@@ -2520,9 +2520,12 @@ gw_status gw_sigma_vjp(gw_ctx* c, const void* V, const gw_z* G, const gw_z* Pt_t
     // P0^{-q}(beta - tau) = P0^q(tau)^T for any G (see pol_impl), so the
     // cotangents of q and -q add up, P0bar^q(tau) + P0bar^{-q}(beta - tau)^T,
     // before one polarization adjoint for both (half of the nodes for q = -q).
-    // With pairs_ok the P~ V of -q comes from that of q as in se_nodes.
-    // Measured with the triple products, 3x3x3, nao 16, naux 150: 249 -> 111 ms.
-    const bool pairs = pairs_ok(c, GW_HERM_FORWARD);
+    // Measured with the triple products, 3x3x3, nao 16, naux 150: 251 -> 116 ms.
+    // Where P~ is rebuilt here, from a G that is Hermitian by the mode's
+    // statement, the P~ V of -q also comes from that of q as in se_nodes.  A
+    // given P~ is read for every q: the mode states nothing of it or of its G
+    // (taking its -q from q gave 103 ms, and a wrong gradient at a general G).
+    const bool pairs = !stored && pairs_ok(c, GW_HERM_FORWARD);
     const long long per = nt * nn;
     // from P~bar(tau) in place to P0bar(tau)
     auto back = [&](gw_z* P, const gw_z* pw) -> gw_status {
