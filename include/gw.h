@@ -40,8 +40,10 @@
  * Spin.  Spin-restricted: ns (1 or 2) multiplies the polarization, the
  *   Hartree term and the electron count; exchange and Sigma~ carry no spin sum.
  * Environment (read by gw_create).  GW_DEBUG_BOUNDS=1 makes every call check
- *   on the host, before launching, that each GEMM descriptor it builds stays
- *   inside the extents of its operands (a failed check returns GW_ERR_ARG);
+ *   on the host, before launching, that each GEMM descriptor it builds, and
+ *   each launch of the fp64 chain's triple products, polarization contraction
+ *   and screened-interaction solves, stays inside its operands (a failed check
+ *   returns GW_ERR_ARG);
  *   GW_TILE_CFG=0..10 forces the tile shape of the two large fp64
  *   contractions (measurement only): 0..4 the four-product complex MFMA form,
  *   5..10 the three-product (Gauss) form (by default the polarization runs by

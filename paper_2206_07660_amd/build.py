@@ -18,7 +18,7 @@ def source_hash():
     import hashlib
     h = hashlib.sha256()
     for f in ("gw_kernels.hip", "gw_sandwich.hip", "gw_polar.hip", "gw_dyson.hip",
-              "gw_wlu.hip", "gw_kernels.h", "gw_device.h", "gw_mu.h", "gw_api.hip"):
+              "gw_wlu.hip", "gw_kernels.h", "gw_device.h", "gw_extents.h", "gw_mu.h", "gw_api.hip"):
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

@@ -14,6 +14,7 @@
 
 #include "../../include/gw.h"
 #include "grids.h"
+#include "gw_extents.h"
 #include "gw_kernels.h"
 #include "gw_mu.h"
 #include "ir.h"
@@ -280,24 +281,39 @@ gw_status run_split(gw_ctx* c, const SplitDesc& d, Ext eA, Ext eB, Ext eC) {
   return prof_end(c, d.tag, e0, 8.0 * outs * d.K * d.batch);
 }
 
+gw_status leaves(gw_ctx* c, const char* what, const char* operand) {
+  return operand ? fail(c, GW_ERR_ARG, std::string("internal descriptor check: ") + what + ": " + operand + " out of bounds")
+                 : GW_OK;
+}
+// host copy of a part of the k+q table, and its entries from there on
+const int* host_tab(const gw_ctx* c, const int* tab) { return c->plus.data() + (tab - c->dplus); }
+long long tab_left(const gw_ctx* c, const int* tab) { return (long long)c->plus.size() - (tab - c->dplus); }
+
 // The triple products (nao x nao matrices) with their profiling class; 6 real
-// flops per complex multiply-add (three real products).
-gw_status sand_prod(gw_ctx* c, SandProd d, int tag) {
+// flops per complex multiply-add (three real products).  The arrays that the
+// operands lie in follow in the operands' order.
+gw_status sand_prod(gw_ctx* c, SandProd d, int tag, Arr V, Arr L, Arr R, Arr Y) {
   d.nk = c->nk; d.naux = c->d.naux; d.nao = c->d.nao;
   d.svk = c->sv;
+  gw_status s;
+  if (c->check_bounds &&
+      (s = leaves(c, "sand_prod", sand_prod_leaves(d, host_tab(c, d.tab), tab_left(c, d.tab), V, L, R, Y))) != GW_OK)
+    return s;
   hipEvent_t e0 = nullptr;
-  gw_status s = prof_begin(c, tag, &e0);
-  if (s != GW_OK) return s;
+  if ((s = prof_begin(c, tag, &e0)) != GW_OK) return s;
   hipError_t e = sand_prod_launch(d, c->st);
   if (e != hipSuccess) return fail(c, GW_ERR_DEVICE, std::string("sand_prod: ") + hipGetErrorString(e));
   return prof_end(c, tag, e0, 12.0 * d.nt * d.nk * c->sv * c->d.nao);
 }
 
-gw_status sand_sum(gw_ctx* c, SandSum d, int tag) {
+gw_status sand_sum(gw_ctx* c, SandSum d, int tag, Arr A, Arr B, Arr G, Arr O, Arr part) {
   d.nk = c->nk; d.naux = c->d.naux; d.nao = c->d.nao;
+  gw_status s;
+  if (c->check_bounds &&
+      (s = leaves(c, "sand_sum", sand_sum_leaves(d, host_tab(c, d.tab), tab_left(c, d.tab), A, B, G, O, part))) != GW_OK)
+    return s;
   hipEvent_t e0 = nullptr;
-  gw_status s = prof_begin(c, tag, &e0);
-  if (s != GW_OK) return s;
+  if ((s = prof_begin(c, tag, &e0)) != GW_OK) return s;
   hipError_t e = sand_sum_launch(d, c->st);
   if (e != hipSuccess) return fail(c, GW_ERR_DEVICE, std::string("sand_sum: ") + hipGetErrorString(e));
   return prof_end(c, tag, e0, 12.0 * d.nt * d.nk * c->sv * c->d.nao);
@@ -1095,9 +1111,9 @@ static gw_status pol_impl(gw_ctx* c, const Work& w, const void* V, const gw_z* G
 
 // P[tl][Q][Q'] = alpha sum_{k,e} Y[tl][k][Q][e] conj(V[k][Q'][e]) of tcur nodes
 // (added to P with accumulate), completed as pol_finish does; Z has room for
-// the Y of tc nodes.
+// the Y of tc nodes.  P and M lie in the arrays Pa and Ma.
 static gw_status pol_contract(gw_ctx* c, const char* Y, char* Z, const char* Vq, int tcur, int tc, double2* P,
-                              double2* M, double alpha, bool accumulate, bool herm) {
+                              double2* M, double alpha, bool accumulate, bool herm, Arr Pa, Arr Ma) {
   const int nk = c->nk, naux = c->d.naux;
   const long long n2 = c->n2, sv = c->sv, S = (long long)nk * sv, nn = (long long)naux * naux;
   const long long room = (long long)tc * S;
@@ -1110,8 +1126,11 @@ static gw_status pol_contract(gw_ctx* c, const char* Y, char* Z, const char* Vq,
     a.tsY = S; a.sv = sv; a.tri = herm; a.accumulate = accumulate;
     a.alpha = alpha;
     hipEvent_t e0 = nullptr;
-    gw_status s = prof_begin(c, KC_POL_CONTRACT, &e0);
-    if (s != GW_OK) return s;
+    gw_status s;
+    if (c->check_bounds &&
+        (s = leaves(c, "pol_acc", pol_acc_leaves(a, room, Arr{Y, tcur * S}, Arr{Vq, S}, Pa, Ma, Arr{Z, room}))) != GW_OK)
+      return s;
+    if ((s = prof_begin(c, KC_POL_CONTRACT, &e0)) != GW_OK) return s;
     HIPCHK(c, pol_acc_launch(a, room, c->st));
     return prof_end(c, KC_POL_CONTRACT, e0, 6.0 * outs * a.K * tcur);
   }
@@ -1166,18 +1185,19 @@ static gw_status pol_nodes(gw_ctx* c, const Work& w, const char* Vd, const char*
       p.nt = tcur; p.tsY = S; p.tabR = 1; p.tsL = -gs; p.tsR = gs;
       p.L = (const double2*)Gbd + (nt - 1 - t0) * gs;
       p.R = (const double2*)Gd + t0 * gs;
-      gw_status s = sand_prod(c, p, KC_POL_PRODUCER);
+      const Arr slab{Aq, S}, y{X, tc * S};
+      gw_status s = sand_prod(c, p, KC_POL_PRODUCER, slab, Arr{Gbd, nt * gs}, Arr{Gd, nt * gs}, y);
       if (s != GW_OK) return s;
       if (Gd2) {
         p.L = (const double2*)Gbd2 + (nt - 1 - t0) * gs;
         p.R = (const double2*)Gd2 + t0 * gs;
         p.accumulate = 1;
-        if ((s = sand_prod(c, p, KC_POL_PRODUCER)) != GW_OK) return s;
+        if ((s = sand_prod(c, p, KC_POL_PRODUCER, slab, Arr{Gbd2, nt * gs}, Arr{Gd2, nt * gs}, y)) != GW_OK) return s;
       }
       const long long nn = (long long)naux * naux;
       if ((s = pol_contract(c, X, Z, Aq, tcur, tc, (double2*)P0 + t0 * nn,
                             M0 ? (double2*)M0 + (nt - 1 - t0) * nn : nullptr, -(double)c->d.ns / nk, accumulate,
-                            herm)) != GW_OK) return s;
+                            herm, Arr{P0, nt * nn}, Arr{M0, nt * nn})) != GW_OK) return s;
       continue;
     }
     // X[tl][k][Q][d][b] = sum_a V[q][k][Q][d][a] G[t0+tl][k+q][a][b]
@@ -1279,6 +1299,15 @@ static gw_status solve_core(gw_ctx* c, const gw_z* P0, gw_z* Pt, const int* sel,
   const long long nn = (long long)n * n;
   double2* Am = (double2*)c->ws;
   double2* Bm = (double2*)Pt;
+  if (c->check_bounds) {
+    // the panel kernels take every matrix of A, and of P0 and Pt by position
+    if ((size_t)nmat * nn * 16 > c->ws_bytes) return leaves(c, "solve", "A");
+    if (sel && (sel < c->dsel || sel + nmat > c->dsel + c->sel.size())) return leaves(c, "solve", "table");
+    for (long long b = 0; sel && b < nmat; ++b) {
+      const int at = c->sel[(sel - c->dsel) + b];
+      if (at < 0 || at >= c->nk * c->d.nw_b) return leaves(c, "solve", "B");
+    }
+  }
   HIPCHK(c, wlu_launch(0, (const double2*)P0, Am, Bm, sel, n, 0, kNb, nmat, c->dflag, c->st));
   auto gemm = [&](double2* X, long long xo, double2* Y, long long yo, double2* Z, long long zo, int M,
                   int N, int K) -> gw_status {
@@ -1483,14 +1512,15 @@ static gw_status se_nodes(gw_ctx* c, const char* Vd, const char* Gd, const gw_z*
       x.part = (double2*)L; x.part_elems = (long long)tc * S;
       x.G = (const double2*)Gd + t0 * gs; x.tsG = gs;
       x.O = (double2*)Sig + t0 * gs; x.tsO = gs; x.tabO = 1;
-      if ((s = sand_sum(c, x, KC_SE_FINAL)) != GW_OK) return s;
+      const Arr slab{Aq, S}, vt{Vt, tc * S}, ga{Gd, nt * gs}, sa{Sig, nt * gs}, part{L, tc * S};
+      if ((s = sand_sum(c, x, KC_SE_FINAL, slab, vt, ga, sa, part)) != GW_OK) return s;
       if (!mirror) continue;
       // -q at the mirrored nodes:
       // Sig[nt-1-t0-tl][kk] += -(1/nk) sum_Q V[q][kk][Q] G[nt-1-t0-tl][kk+q] Vt[tl][Q][kk]^H
       x.bh = 1;
       x.G = (const double2*)Gd + (nt - 1 - t0) * gs; x.tsG = -gs; x.tabG = 1;
       x.O = (double2*)Sig + (nt - 1 - t0) * gs; x.tsO = -gs; x.tabO = 0;
-      if ((s = sand_sum(c, x, KC_SE_FINAL)) != GW_OK) return s;
+      if ((s = sand_sum(c, x, KC_SE_FINAL, slab, vt, ga, sa, part)) != GW_OK) return s;
       continue;
     }
     // L[tl][kk][i][Q][b] = sum_a conj(V[q][kk][Q][a][i]) G[t0+tl][kk][a][b]
@@ -1600,7 +1630,8 @@ static gw_status exchange(gw_ctx* c, const char* Vd, const double2* X, double2* 
     x.G = X; x.O = O; x.part = T; x.part_elems = nk * c->sv;
     if (fold) { x.bh = 1; x.tabG = 1; x.fold_t = 1; }
     else x.tabO = 1;
-    gw_status s = sand_sum(c, x, KC_HF);
+    const Arr v{Vd, nk * (nk * c->sv)};
+    gw_status s = sand_sum(c, x, KC_HF, v, v, Arr{X, nk * c->n2}, Arr{O, nk * c->n2}, Arr{T, nk * c->sv});
     if (s != GW_OK) return s;
   }
   return GW_OK;
@@ -1810,12 +1841,13 @@ static gw_status se_vjp_g(gw_ctx* c, const gw_z* Vq, const gw_z* Pt, const gw_z*
     x.bh = 1;
     x.G = (const double2*)Sbar + t0 * gs; x.tsG = gs; x.tabG = 1;
     x.O = (double2*)Gbar + t0 * gs; x.tsO = gs;
-    if ((s = sand_sum(c, x, KC_SE_FINAL)) != GW_OK) return s;
+    const Arr slab{Vq, S}, vt{Vt, tc * S}, sa{Sbar, nt * gs}, ga{Gbar, nt * gs}, part{x.part, tc * S};
+    if ((s = sand_sum(c, x, KC_SE_FINAL, slab, vt, sa, ga, part)) != GW_OK) return s;
     if (!pair) continue;
     x.bh = 0;
     x.G = (const double2*)Sbar + (nt - 1 - t0) * gs; x.tsG = -gs; x.tabG = 0;
     x.O = (double2*)Gbar + (nt - 1 - t0) * gs; x.tsO = -gs; x.tabO = 1;
-    if ((s = sand_sum(c, x, KC_SE_FINAL)) != GW_OK) return s;
+    if ((s = sand_sum(c, x, KC_SE_FINAL, slab, vt, sa, ga, part)) != GW_OK) return s;
   }
   return GW_OK;
 }
@@ -1830,10 +1862,11 @@ static gw_status se_vjp_p(gw_ctx* c, const gw_z* Vq, const gw_z* G, const gw_z* 
     p.nt = tcur; p.tsY = S;
     p.L = (const double2*)G + t0 * gs; p.tsL = gs; p.hermL = 1;
     p.R = (const double2*)Sbar + t0 * gs; p.tsR = gs; p.tabR = 1;
-    gw_status s = sand_prod(c, p, KC_SE_PRODUCER);
+    gw_status s = sand_prod(c, p, KC_SE_PRODUCER, Arr{Vq, S}, Arr{G, nt * gs}, Arr{Sbar, nt * gs}, Arr{c->ws, tc * S});
     if (s != GW_OK) return s;
+    const long long nn = (long long)c->d.naux * c->d.naux;
     if ((s = pol_contract(c, (char*)c->ws, (char*)c->ws + region_bytes(c, tc), (const char*)Vq, tcur, tc,
-                          (double2*)Ptbar + (long long)t0 * c->d.naux * c->d.naux, nullptr, -1.0 / nk, false, false)) != GW_OK)
+                          (double2*)Ptbar + t0 * nn, nullptr, -1.0 / nk, false, false, Arr{Ptbar, nt * nn}, Arr{})) != GW_OK)
       return s;
   }
   return GW_OK;
@@ -1858,12 +1891,13 @@ static gw_status pol_vjp_q(gw_ctx* c, const gw_z* Vq, const gw_z* G, const gw_z*
     x.part = (double2*)((char*)c->ws + region_bytes(c, tc)); x.part_elems = (long long)tc * S;
     x.G = (const double2*)G + (nt - 1 - t0) * gs; x.tsG = -gs;
     x.O = (double2*)Gbar + t0 * gs; x.tsO = gs; x.tabO = 1;
-    if ((s = sand_sum(c, x, KC_SE_FINAL)) != GW_OK) return s;
+    const Arr slab{Vq, S}, pv{c->ws, tc * S}, ga{G, nt * gs}, gb{Gbar, nt * gs}, part{x.part, tc * S};
+    if ((s = sand_sum(c, x, KC_SE_FINAL, slab, pv, ga, gb, part)) != GW_OK) return s;
     if ((s = times_v(c, Pb, Vq, (char*)c->ws, tcur, true)) != GW_OK) return s;
     x.bh = 1;
     x.G = (const double2*)G + t0 * gs; x.tsG = gs; x.tabG = 1;
     x.O = (double2*)Gbar + (nt - 1 - t0) * gs; x.tsO = -gs; x.tabO = 0;
-    if ((s = sand_sum(c, x, KC_SE_FINAL)) != GW_OK) return s;
+    if ((s = sand_sum(c, x, KC_SE_FINAL, slab, pv, ga, gb, part)) != GW_OK) return s;
   }
   return GW_OK;
 }
