@@ -146,9 +146,8 @@ struct DysonArgs {
 };
 
 // Y[t][k][Q] = L V[k][Q] R for t < nt, k < nk, Q < naux (nao x nao matrices,
-// complex128).  L and R are the matrices L + t tsL + k' nao^2 and
-// R + t tsR + k' nao^2 with k' = k, or tab[k] where tabL / tabR is set; hermL
-// takes L^H.  V and Y have k stride svk and Q stride nao^2, Y the t stride
+// complex128).  L and R are the matrices L + t tsL + k nao^2 and
+// R + t tsR + k' nao^2 with k' = k, or tab[k] where tabR is set; hermL takes L^H.  V and Y have k stride svk and Q stride nao^2, Y the t stride
 // tsY.  accumulate adds to Y.
 struct SandProd {
   const double2 *V, *L, *R;
@@ -156,7 +155,7 @@ struct SandProd {
   const int* tab;
   int nt, nk, naux, nao;
   long long svk, tsL, tsR, tsY;
-  int tabL, tabR, hermL, accumulate;
+  int tabR, hermL, accumulate;
   int qlen;           // filled by the launcher: Q per workgroup
 };
 

@@ -52,6 +52,13 @@ template <bool CJ = false> __device__ __forceinline__ Frag acc3_frag(const Acc3&
   return Frag{re, s - re, s};
 }
 
+// x + a b
+__device__ __forceinline__ double2 cfma(double2 a, double2 b, double2 x) {
+  x.x = __builtin_fma(-a.y, b.y, __builtin_fma(a.x, b.x, x.x));
+  x.y = __builtin_fma(a.y, b.x, __builtin_fma(a.x, b.y, x.y));
+  return x;
+}
+
 // Fragments of a small matrix in LDS, zero past nao.  ROWS: lane l of
 // fragment (b, s) holds M[16 b + l % 16][4 s + l / 16] (an A operand),
 // otherwise M[4 s + l / 16][16 b + l % 16] (a B operand); herm: of M^H.
@@ -105,7 +112,7 @@ __global__ void __launch_bounds__(64 * Waves<(KS + 3) / 4>::n) sand_prod_k(SandP
   const int n = d.nao, n2 = n * n;
   const SandPos p = sand_pos(d.nt, d.nk, d.naux, d.qlen);
   const int kq = d.tab[p.k];
-  lds_fragments<NB, KS, true>(ldsL, d.L + p.t * d.tsL + (long long)(d.tabL ? kq : p.k) * n2, n, d.hermL != 0, NT);
+  lds_fragments<NB, KS, true>(ldsL, d.L + p.t * d.tsL + (long long)p.k * n2, n, d.hermL != 0, NT);
   lds_fragments<NB, KS, false>(ldsR, d.R + p.t * d.tsR + (long long)(d.tabR ? kq : p.k) * n2, n, false, NT);
   __syncthreads();
   const int lane = threadIdx.x & 63, r16 = lane & 15, kl = lane >> 4;
@@ -188,6 +195,50 @@ __global__ void __launch_bounds__(64 * Waves<(KS + 3) / 4>::n) sand_prod_k(SandP
         }
       }
     }
+  }
+}
+
+// Y = L V R of matrices of N <= 4 orbitals, a thread per row of a Y_Q on vector
+// instructions: a 16 x 16 block of sand_prod_k would hold one such matrix and
+// take 0.43 ns of the chip whatever its size.  Bound by the stores of Y (a row
+// is contiguous, and the rows of a wave are); L and R of (t, k) are read from
+// LDS by all lanes at once.  One q of the polarization at 4x4x4, naux 220, 100
+// nodes, 1 / 2 / 3 / 4 orbitals: 626 / 786 / 1066 / 1298 us with sand_prod_k, 109
+// / 282 / 608 / 952 with this one; from 5 orbitals on sand_prod_k is the faster.
+template <int N>
+__global__ void __launch_bounds__(256) sand_small_k(SandProd d, int chunks) {
+  __shared__ double2 sL[N * N], sR[N * N];
+  const int chunk = blockIdx.x % chunks, r = blockIdx.x / chunks;
+  const int k = r % d.nk, t = r / d.nk, kq = d.tab[k];
+  constexpr int n2 = N * N;
+  if (threadIdx.x < n2) {
+    const int i = threadIdx.x / N, j = threadIdx.x % N;
+    double2 l = d.L[t * d.tsL + (long long)k * n2 + (d.hermL ? j * N + i : i * N + j)];
+    if (d.hermL) l.y = -l.y;
+    sL[threadIdx.x] = l;
+    sR[threadIdx.x] = d.R[t * d.tsR + (long long)(d.tabR ? kq : k) * n2 + threadIdx.x];
+  }
+  __syncthreads();
+  const int e = chunk * (int)blockDim.x + threadIdx.x;
+  if (e >= d.naux * N) return;
+  const int Q = e / N, c = e - Q * N;
+  const double2* V = d.V + k * d.svk + (long long)Q * n2;
+  double2 u[N];
+#pragma unroll
+  for (int a = 0; a < N; ++a) u[a] = double2{0.0, 0.0};
+#pragma unroll
+  for (int x = 0; x < N; ++x) {
+    const double2 l = sL[c * N + x];
+#pragma unroll
+    for (int a = 0; a < N; ++a) u[a] = cfma(l, V[x * N + a], u[a]);
+  }
+  double2* y = d.Y + t * d.tsY + k * d.svk + (long long)Q * n2 + c * N;
+#pragma unroll
+  for (int b = 0; b < N; ++b) {
+    double2 v = d.accumulate ? y[b] : double2{0.0, 0.0};
+#pragma unroll
+    for (int a = 0; a < N; ++a) v = cfma(u[a], sR[a * N + b], v);
+    y[b] = v;
   }
 }
 
@@ -445,6 +496,17 @@ hipError_t sand_prod_launch(const SandProd& d0, hipStream_t st) {
   if (d0.nt <= 0 || d0.nk <= 0 || d0.naux <= 0) return hipSuccess;
   if (d0.nao < 1 || d0.nao > 60) return hipErrorInvalidValue;
   SandProd d = d0;
+  if (d.nao <= 4) {
+    const int rows = d.naux * d.nao, nt = std::min(256, (rows + 63) / 64 * 64), chunks = (rows + nt - 1) / nt;
+    const long long wgs = (long long)d.nt * d.nk * chunks;
+    if (wgs > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    const dim3 grid((unsigned)wgs);
+    if (d.nao == 1) sand_small_k<1><<<grid, nt, 0, st>>>(d, chunks);
+    else if (d.nao == 2) sand_small_k<2><<<grid, nt, 0, st>>>(d, chunks);
+    else if (d.nao == 3) sand_small_k<3><<<grid, nt, 0, st>>>(d, chunks);
+    else sand_small_k<4><<<grid, nt, 0, st>>>(d, chunks);
+    return hipGetLastError();
+  }
   // Q ranges: as long as 2048 workgroups remain (the LDS fill costs about two
   // Q), but not below 8
   const long long base = (long long)d.nt * d.nk;
