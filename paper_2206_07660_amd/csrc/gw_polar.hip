@@ -22,7 +22,10 @@
 // two waves of a SIMD rarely leave its pipe together.  Measured for one q (ms,
 // 64 x 64 tiles of zgemm_k with four products before): 18.0 vs 22.5 at 4x4x4,
 // nao 26, naux 250, 100 nodes (0.70 of the MFMA peak executed); 0.69 vs 1.76 at
-// 3x3x3, nao 16, naux 150, 60 nodes.
+// 3x3x3, nao 16, naux 150, 60 nodes.  A short K sum that leaves most of
+// the chip idle is cut into smaller parts (general / Hermitian G at 2x2x2, nao
+// 4, naux 150, 20 nodes, us a call: 45 / 49 on the tiles, 71 / 48 on parts of
+// 56 blocks, 40 / 29 on parts of 8).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -374,30 +377,40 @@ hipError_t pol_acc_launch(const PolAcc& d0, long long part_elems, hipStream_t st
   // 74 KB of LDS, two workgroups per CU), otherwise eight and as many parts as
   // keep a wave at 7 blocks
   const int W = d.nblk <= 6 ? 1 : d.nblk <= 12 ? 2 : d.nblk <= 24 ? 4 : 8;
-  d.per = W == 8 ? kPartBlk : 6 * W;
-  d.nparts = 0;
-  int M = 1;                       // blocks of a wave
-  each_pair(d.nb, d.ns, d.tri != 0, [&](int, int, int rows, int cols, bool diag) {
-    const int n = pair_blocks(rows, cols, diag), np = (n + d.per - 1) / d.per;
-    d.nparts += np;
-    M = std::max(M, ((n + np - 1) / np + W - 1) / W);
-    return false;
-  });
-  // K parts: two waves per SIMD run at once; the count that ends its rounds
-  // of workgroups soonest (a part costs about 12 steps of start and end)
-  const long long slots = W == 8 ? 256 : W == 1 ? 1024 : 512, wgs = (long long)d.nparts * d.nt;
+  const long long slots = W == 8 ? 256 : W == 1 ? 1024 : 512;
   const int steps = (d.K + 7) / 8;
   const long long room = part_elems / ((long long)d.nt * d.nblk * 256);
-  int best = 1;
+  // K parts: two waves per SIMD run at once; the count that ends its rounds
+  // of workgroups soonest (a part costs about 12 steps of start and end).
+  // Where that leaves half of the chip idle (a short K sum: few steps, and
+  // room for few partial sums) the blocks are dealt to more workgroups, down to
+  // one block per wave; a step costs about one block more than it has.
+  int M = 1, split = 1;            // blocks of a wave, K parts
+  long long wgs = 0;
   double cost = 0.0;
-  for (int s = 1; s <= 64 && s <= room && s <= steps; ++s) {
-    const double c = (double)((wgs * s + slots - 1) / slots) * ((steps + s - 1) / s + 12);
-    if (s == 1 || c < cost) {
-      best = s;
-      cost = c;
+  for (int per = W == 8 ? kPartBlk : 6 * W;; per = per == kPartBlk ? 32 : per / 2) {
+    int nparts = 0, m = 1;
+    each_pair(d.nb, d.ns, d.tri != 0, [&](int, int, int rows, int cols, bool diag) {
+      const int n = pair_blocks(rows, cols, diag), np = (n + per - 1) / per;
+      nparts += np;
+      m = std::max(m, ((n + np - 1) / np + W - 1) / W);
+      return false;
+    });
+    const long long w = (long long)nparts * d.nt;
+    for (int s = 1; s <= 64 && s <= room && s <= steps; ++s) {
+      const double c = (double)((w * s + slots - 1) / slots) * ((steps + s - 1) / s + 12) * (m + 1);
+      if (wgs == 0 || c < cost) {
+        cost = c;
+        split = s;
+        M = m;
+        wgs = w;
+        d.per = per;
+        d.nparts = nparts;
+      }
     }
+    if (W < 8 || per <= W || 2 * wgs * split > slots) break;
   }
-  d.steps = (steps + best - 1) / best;
+  d.steps = (steps + split - 1) / split;
   d.nsplit = (steps + d.steps - 1) / d.steps;
   if (wgs * d.nsplit > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)(wgs * d.nsplit));
@@ -410,7 +423,9 @@ hipError_t pol_acc_launch(const PolAcc& d0, long long part_elems, hipStream_t st
     if (M == 7) POL_CALL(8, 3, 7);
     else if (M == 6) POL_CALL(8, 3, 6);
     else if (M == 5) POL_CALL(8, 3, 5);
-    else POL_CALL(8, 3, 4);
+    else if (M > 2) POL_CALL(8, 3, 4);
+    else if (M == 2) POL_CALL(8, 3, 2);
+    else POL_CALL(8, 3, 1);
   } else if (W == 4) {
     if (M == 6) POL_CALL(4, 3, 6);
     else POL_CALL(4, 3, 4);
