@@ -868,11 +868,34 @@ static hipError_t launch_cfg(const GemmDesc& d0, hipStream_t st) {
 // from the three-product form (11.7 vs 12.0 ms), their stores bound them.
 // Whether the last 64-row tile of M rows is at most half full.
 static bool half_rows(int M) { return (M - 1) % 64 < 32; }
-// Whether 32 x 32 tiles execute less than 0.8 of what 64 x 64 tiles do of a
-// triangle; the smaller tiles read their operands twice as often.
-static bool small_triangle(int tri, int M) {
+// Workgroups per CU of a triangle's 32 x 32 (n32) and 64 x 64 (n64) tiles over
+// nt nodes, rounded up; 0 and 0 unless the small tiles execute less than 0.8 of
+// what the large ones do (they read their operands twice as often).
+static void triangle_load(int tri, int M, int nt, long long& n32, long long& n64) {
   const long long b = (M + 31) / 32, t = (M + 63) / 64;
-  return tri && 5 * b * (b + 1) < 16 * t * (t + 1);
+  n32 = n64 = 0;
+  if (!tri || 5 * b * (b + 1) >= 16 * t * (t + 1)) return;
+  n32 = (b * (b + 1) / 2 * nt + 255) / 256;
+  n64 = (t * (t + 1) / 2 * nt + 255) / 256;
+}
+// fp32: a CU runs one large tile at a time and several small ones, the whole
+// product in units of a large tile at 1 / 2 / 3 / 4 of them per CU: 1.0 / 2.0 /
+// 3.0 / 4.1, at 1 .. 7 small ones: 0.7, 0.9, 1.1 (up to 1.45), 1.2, 1.5, 1.8, 2.1.
+static bool small_triangle_f32(int tri, int M, int nt) {
+  long long n32, n64;
+  triangle_load(tri, M, nt, n32, n64);
+  return n64 > 1 || (n64 == 1 && n32 < 3);
+}
+// bf16x3: two large or four small tiles run on a CU at a time: 1.0 / 1.35 / 2.3
+// / 2.9 against 0.9, 1.0, 1.1, 1.2, then 1.9, 2.1, 2.0, .. 2.9 (11).  One
+// large tile per CU is won back only by long sums (1.03 .. 1.08 of its time at
+// K 2048, 0.9 above 4096), and short ones are all start and end.
+static bool small_triangle_bf16(int tri, int M, int nt, int K) {
+  long long n32, n64;
+  triangle_load(tri, M, nt, n32, n64);
+  if (n64 == 1) return K > 4096;
+  if (n64 == 2) return n32 <= 4 && K >= 256;
+  return n64 == 3 && K >= 512;
 }
 
 template <int TAG, class TA, class TB, class TC, bool F32>
@@ -912,7 +935,7 @@ static hipError_t launch_typed(const GemmDesc& d, hipStream_t st) {
     if constexpr (TAG == KC_SE_CONTRACT) {
       if (d.cfg >= 5 && d.cfg <= 10 && half_rows(d.M)) return launch_cfg<1, 2, 2, 2, 2, TAG, TA, TB, TC, F32, true>(d, st);
     } else {
-      if (small_triangle(d.tri, d.M)) return launch_cfg<1, 1, 2, 2, 2, TAG, TA, TB, TC, F32>(d, st);
+      if (small_triangle_f32(d.tri, d.M, d.batch)) return launch_cfg<1, 1, 2, 2, 2, TAG, TA, TB, TC, F32>(d, st);
     }
     if (d.cfg >= 5 && d.cfg <= 10) return launch_cfg<2, 2, 2, 2, 2, TAG, TA, TB, TC, F32, true>(d, st);
     return launch_cfg<2, 2, 2, 2, 2, TAG, TA, TB, TC, F32>(d, st);
@@ -1351,7 +1374,7 @@ hipError_t bsgemm_launch(const SplitDesc& d, hipStream_t st) {
   if (d.tag == KC_POL_CONTRACT && d.ta == 1 && d.tb == 1 && d.tc == 0) {
     // half-empty tiles on the diagonal and at the edge: 32 x 32 ones (naux 150
     // at 3x3x3, nao 16, 60 nodes: 406 -> 337 us per q; the same sums)
-    if (small_triangle(d.tri, d.M)) return bs_cfg<1, 1, 2, 2, KC_POL_CONTRACT, float2, float2, double2, true, true, true, float, 2>(d, st);
+    if (small_triangle_bf16(d.tri, d.M, d.batch, d.K)) return bs_cfg<1, 1, 2, 2, KC_POL_CONTRACT, float2, float2, double2, true, true, true, float, 2>(d, st);
     return bs_cfg<2, 2, 2, 2, KC_POL_CONTRACT, float2, float2, double2, true, true, true, float, 2>(d, st);
   }
   if (d.tag == KC_SE_CONTRACT && d.ta == 1 && d.tb == 1 && d.tc == 1) {
