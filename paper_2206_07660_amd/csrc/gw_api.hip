@@ -1336,7 +1336,9 @@ static gw_status solve_core(gw_ctx* c, const gw_z* P0, gw_z* Pt, const int* sel,
     // update reads and writes all of the trailing A and B and is bound by that
     // (404 matrices of order 250, with the back substitution by pairs of blocks:
     // 4.04 -> 3.30 ms)
-    const bool small = n - j0 <= 512, two = small && n - j0 > 2 * kNb;
+    // (2624 matrices of order 4: 62 us a solve on the general panel, 70 on the
+    // register-resident one, whose start costs more than so few columns)
+    const bool small = n > 8 && n - j0 <= 512, two = small && n - j0 > 2 * kNb;
     const int j1 = std::min(j0 + (two ? 2 : 1) * kNb, n), w = j1 - j0, rest = n - j1;
     if (small) {
       HIPCHK(c, wlu_factor_launch(Am, Bm, sel, n, j0, false, nmat, c->dflag, c->st));
