@@ -2406,6 +2406,7 @@ gw_status gw_sigma(gw_ctx* c, const void* V, const gw_z* G, gw_z* gamma, gw_z* S
   const bool stored = P_tau || P0_iw || Pt_iw;
   if (stored && !(P_tau && P0_iw && Pt_iw))
     return fail(c, GW_ERR_ARG, "P_tau, P0_iw and Pt_iw are given all together or not at all");
+  if (stored && P0_iw == Pt_iw) return fail(c, GW_ERR_ARG, "Pt_iw may not alias P0_iw");
   if (phi) *phi = 0.0;
   const int nk = c->nk, naux = c->d.naux;
   const long long nn = (long long)naux * naux;
