@@ -15,6 +15,20 @@ __device__ __forceinline__ long long map3(const Map3& m, unsigned i) {
   return (long long)c * m.sout + (long long)b * m.smid + (long long)a * m.sin;
 }
 
+__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
+  return double2{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
+}
+
+// the larger of x and that of the lane which the DPP control CTRL names
+template <int CTRL> __device__ __forceinline__ unsigned dpp_max(unsigned x) {
+  return max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false));
+}
+
+// accumulators of a three-product (Gauss) complex product
+struct Acc3 {
+  d4 p1, p2, p3;
+};
+
 __device__ __forceinline__ double2 to_d2(double2 v) { return v; }
 __device__ __forceinline__ double2 to_d2(float2 v) { return double2{(double)v.x, (double)v.y}; }
 __device__ __forceinline__ float2 to_f2(double2 v) { return float2{(float)v.x, (float)v.y}; }

@@ -19,16 +19,10 @@
 
 namespace {
 
-__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-  return double2{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
-}
 __device__ __forceinline__ double readlane_d(double x, int l) {
   const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
   const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, l), hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), l);
   return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
-}
-template <int CTRL> __device__ __forceinline__ unsigned dpp_max(unsigned x) {
-  return max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false));
 }
 // largest x over each aligned group of R lanes
 template <int R> __device__ __forceinline__ unsigned group_max(unsigned x) {

@@ -965,7 +965,6 @@ static hipError_t launch_tag(const GemmDesc& d, hipStream_t st) {
     if (code == 0) return launch_typed<TAG, double2, double2, double2, false>(d, st);
   }
   if constexpr (TAG == KC_HF) {
-    if (code == 1) return launch_typed<TAG, float2, double2, double2, false>(d, st);
     if (code == 2) return launch_typed<TAG, double2, float2, double2, false>(d, st);
   }
   if constexpr (TAG == KC_POL_PRODUCER || TAG == KC_SE_PRODUCER) {

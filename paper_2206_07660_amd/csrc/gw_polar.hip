@@ -94,10 +94,6 @@ __host__ __device__ inline void block_rc(int cols, bool diag, int b, int& r, int
   }
 }
 
-struct Acc3 {
-  d4 p1, p2, p3;
-};
-
 // One element of a fragment in LDS; the 24-byte lane stride visits every bank
 // once per 32 lanes.
 struct Elem {

@@ -35,9 +35,6 @@ template <bool CJ = false> __device__ __forceinline__ Frag frag(double2 v) {
 // a fragment as stored in LDS, with or without its sum
 __device__ __forceinline__ void put_frag(Frag& d, double2 v) { d = frag(v); }
 __device__ __forceinline__ void put_frag(double2& d, double2 v) { d = v; }
-struct Acc3 {
-  d4 p1, p2, p3;
-};
 __device__ __forceinline__ Acc3 acc3_zero() { return Acc3{d4{0, 0, 0, 0}, d4{0, 0, 0, 0}, d4{0, 0, 0, 0}}; }
 __device__ __forceinline__ void mma3(const Frag& a, const Frag& b, Acc3& c) {
   c.p1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.r, b.r, c.p1, 0, 0, 0);

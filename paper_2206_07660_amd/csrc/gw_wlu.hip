@@ -23,9 +23,6 @@ namespace {
 constexpr int kNb = 32;
 constexpr int kWaveOrder = 48;
 
-__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-  return double2{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
-}
 // x - a b
 __device__ __forceinline__ double2 cfnma(double2 a, double2 b, double2 x) {
   x.x = __builtin_fma(a.y, b.y, __builtin_fma(-a.x, b.x, x.x));
@@ -35,9 +32,6 @@ __device__ __forceinline__ double2 cfnma(double2 a, double2 b, double2 x) {
 __device__ __forceinline__ double2 cinv(double2 a) {
   const double den = a.x * a.x + a.y * a.y;
   return den > 0.0 ? double2{a.x / den, -a.y / den} : double2{0.0, 0.0};
-}
-template <int CTRL> __device__ __forceinline__ unsigned dpp_max(unsigned x) {
-  return max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false));
 }
 __device__ __forceinline__ unsigned wave_max(unsigned x) {
   x = dpp_max<0xB1>(x);                      // lane ^ 1
