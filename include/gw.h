@@ -47,9 +47,8 @@
  *   GW_TILE_CFG=0..10 forces the tile shape of the two large fp64
  *   contractions (measurement only): 0..4 the four-product complex MFMA form,
  *   5..10 the three-product (Gauss) form (by default the polarization runs by
- *   16 x 16 blocks, the self-energy on 7, or on 10 where a 64-row tile would
- *   be at most half full); the Hermitian polarization needs a square shape:
- *   0, 4 or 5.  GW_PROD_TILES=1 runs the fp32 producers on the tiled GEMM
+ *   16 x 16 blocks, the self-energy on 7, or on 10 where that executes less);
+ *   the Hermitian polarization needs a square shape: 0, 4 or 5.  GW_PROD_TILES=1 runs the fp32 producers on the tiled GEMM
  *   instead of the streaming kernel.  GW_SPLIT_CFG selects split-bf16 tiles:
  *   bf16x3 self-energy 0 = 128x128 (default), 1 = 64x64, 2 = 128x64; bf16x6
  *   1 = two LDS stages instead of one.  GW_SPLIT_GROUP=g > 0 walks the

@@ -70,8 +70,8 @@ struct gw_ctx {
   int *dplus = nullptr, *dminus = nullptr;
   int* dflag = nullptr;
   double* dpart = nullptr;   // nw_f * nk partials, then the reduced scalar at [nw_f*nk]
-  int nmu = 1;               // values of mu that one electron-count launch takes
-  double* dcnt = nullptr;    // nmu * nw_f * nk partials of electron counts
+  MuCounts mu{1, 1};         // values of mu that one electron-count launch takes
+  double* dcnt = nullptr;    // nw_f * nk partials of the electron counts of a launch
   double* hcnt = nullptr;    // pinned host memory: the counts
   double* dred = nullptr;    // 2 * 1024 partials + 2 results for gw_dot
   double* dphi = nullptr;    // Nk * nw_b per-matrix terms of Phi~, then their sum
@@ -332,7 +332,7 @@ gw_status read_flag(gw_ctx* c, const char* what) {
 }
 
 // Dyson matrices at nmu values of mu: nao <= 32 on the wave-per-matrix kernel,
-// larger ones (nmu = 1, see mu_batch) a workgroup each.
+// larger ones (nmu = 1, see mu_counts) a workgroup each.
 hipError_t dyson_any(gw_ctx* c, const DysonArgs& a, int nmu) {
   if (c->d.nao <= 32) return dyson_reg_launch(a, c->d.nw_f, nmu, c->st);
   return nmu == 1 ? dyson_launch(a, c->d.nw_f, c->st) : hipErrorInvalidValue;
@@ -343,7 +343,7 @@ struct Count {
   gw_ctx* c;
   const gw_z *H0, *S, *Sinf, *Siw;
 
-  // counts at n <= c->nmu values in one launch (G written for n = 1, if given),
+  // counts at n values in one launch (G written for n = 1, if given),
   // with a zero pivot left to count_status or to the flag
   gw_status at(const double* mu, int n, double* ne, gw_z* Gout = nullptr) const {
     DysonArgs a{};
@@ -445,13 +445,14 @@ gw_status gw_create(const gw_dims* d, void* hip_stream, gw_ctx** out) {
     const char* gg = std::getenv("GW_SPLIT_GROUP");
     c->split_group = gg ? std::atoi(gg) : 0;
   }
-  c->nmu = mu_batch(d->nao, (long long)d->nw_f * c->nk);
+  c->mu = mu_counts(d->nao, (long long)d->nw_f * c->nk);
+  const size_t counts = (size_t)std::max(c->mu.batch, c->mu.ahead) * d->nw_f * c->nk;
   if (upload(c, &c->dplus, plus.data(), plus.size() * sizeof(int)) != GW_OK ||
       upload(c, &c->dminus, minus.data(), minus.size() * sizeof(int)) != GW_OK ||
       hipMalloc((void**)&c->dflag, sizeof(int)) != hipSuccess ||
       hipMemset(c->dflag, 0, sizeof(int)) != hipSuccess ||
       hipMalloc((void**)&c->dpart, ((size_t)d->nw_f * c->nk + 8) * sizeof(double)) != hipSuccess ||
-      hipMalloc((void**)&c->dcnt, (size_t)c->nmu * d->nw_f * c->nk * sizeof(double)) != hipSuccess ||
+      hipMalloc((void**)&c->dcnt, counts * sizeof(double)) != hipSuccess ||
       hipHostMalloc((void**)&c->hcnt, 16 * sizeof(double), hipHostMallocMapped) != hipSuccess ||
       hipMalloc((void**)&c->dred, (2 * 1024 + 8) * sizeof(double)) != hipSuccess ||
       hipMalloc((void**)&c->dphi, ((size_t)d->nw_b * c->nk + 8) * sizeof(double)) != hipSuccess) {
@@ -1714,7 +1715,7 @@ gw_status gw_find_mu(gw_ctx* c, const gw_z* H0, const gw_z* S, const gw_z* Sinf,
   gw_status s;
   const Count count{c, H0, S, Sinf, Siw};
   auto root = [&](double target, double* out) {
-    MuRoot<Count> r{count, c->nmu, target, tol};
+    MuRoot<Count> r{count, c->mu.batch, c->mu.ahead, target, tol};
     const gw_status e = r.find(mu0, out);
     return e == GW_OK || !*r.why ? e : fail(c, e, r.why);
   };

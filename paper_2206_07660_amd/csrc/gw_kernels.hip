@@ -859,8 +859,9 @@ static hipError_t launch_cfg(const GemmDesc& d0, hipStream_t st) {
 // the configuration in d.cfg
 // (0: 64x64, 1: 64x128, 2: 128x64, 3: 128x64 on eight waves, 4: 64x64 with
 // two-way split K; 5..9 the three-product form on 64x64, 64x128, 64x96,
-// 128x64 on eight waves, 128x64; 10: 32x192, for a last 64-row tile at most
-// half full: naux 150 at 3x3x3, nao 16, 60 nodes 955 vs 1125 us per q (7)).  Measured at si-4x4x4 (ms per q, fp64):
+// 128x64 on eight waves, 128x64; 10: 32x192, where a last 64-row tile would be
+// at most half full: naux 150 at 3x3x3, nao 16, 60 nodes 955 vs 1125 us per q
+// (7)).  Measured at si-4x4x4 (ms per q, fp64):
 // polarization 22.6 (0) vs 23.3 (5), 28.0 (4); self-energy 31.7 (1) vs 25.7
 // (7), 27.2 (5), 28.6 (8), 34.5 (6), 35.2 (9) -- 6 and 9 need more than 256
 // VGPRs and run one wave per SIMD; loads two K-steps ahead (a third register

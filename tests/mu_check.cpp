@@ -13,15 +13,21 @@ static int bad = 0;
 
 using Fn = std::function<double(double)>;
 
-// matrices of more than 32 orbitals are inverted one mu after another
+// matrices of more than 32 orbitals are inverted one mu after another, and a
+// launch's partial sums stay within 2 MB (or one count)
 static void batch_rule() {
-  for (long long m : {2LL, 24LL, 273LL, 274LL, 1000LL, 4096LL, 4097LL, 6400LL, 2048LL * 262144LL})
+  for (long long m : {2LL, 24LL, 273LL, 1000LL, 4096LL, 6400LL, 65536LL, 2048LL * 262144LL})
     for (int nao = 1; nao <= 60; ++nao) {
-      const int b = mu_batch(nao, m);
-      CHECK(b >= 1 && b <= kMuBatch);
-      CHECK(nao <= 32 ? b == 1 || b * m <= 4096 : b == 1);
+      const MuCounts c = mu_counts(nao, m);
+      CHECK(c.batch >= 1 && c.ahead >= c.batch && c.ahead <= kMuBatch);
+      CHECK(c.ahead == 1 || c.ahead * m <= 262144);
+      if (nao > 32) CHECK(c.ahead == 1);
     }
-  CHECK(mu_batch(32, 273) == 15 && mu_batch(32, 1000) == 4 && mu_batch(32, 6400) == 1);
+  auto is = [](int nao, long long m, int batch, int ahead) {
+    const MuCounts c = mu_counts(nao, m);
+    return c.batch == batch && c.ahead == ahead;
+  };
+  CHECK(is(6, 192, 15, 15) && is(8, 1000, 7, 15) && is(12, 1200, 3, 15) && is(20, 1200, 1, 15) && is(26, 1200, 1, 1));
 }
 
 // the plain bisection, and how many counts it asks for
@@ -71,21 +77,22 @@ static void same(const char* name, const Fn& f, double target, double tol, doubl
   double want = 0.0;
   int np = 0;
   const gw_status ws = plain(f, target, tol, mu0, &want, &np);
-  for (int batch : {1, 2, 3, 4, 7, 8, 14, 15}) {
+  for (int batch : {1, 2, 3, 4, 7, 8, 14, 15})
+  for (int ahead : {batch, 15}) {
     int launches = 0, counts = 0;
     double got = 0.0;
-    MuRoot<Given> r{Given{&f, batch, &launches, &counts}, batch, target, tol};
+    MuRoot<Given> r{Given{&f, std::max(batch, ahead), &launches, &counts}, batch, ahead, target, tol};
     const gw_status s = r.find(mu0, &got);
     CHECK(s == ws);
     CHECK(s == GW_OK ? got == want : *r.why != 0);
     CHECK(launches <= np);
-    if (batch == 1 && s == GW_OK) CHECK(launches == np && counts == np);
+    if (ahead == 1 && s == GW_OK) CHECK(launches == np && counts == np);
     if (batch == 15 && launches > most) {
       ++bad;
       printf("%s: %d launches\n", name, launches);
     }
-    if (s == GW_OK && (batch == 1 || batch == 4 || batch == 15))
-      printf("%-10s batch %2d: %3d launches, %3d counts\n", name, batch, launches, counts);
+    if (s == GW_OK && (batch == 1 || batch == 3 || batch == 15))
+      printf("%-10s batch %2d ahead %2d: %3d launches, %3d counts\n", name, batch, ahead, launches, counts);
   }
 }
 

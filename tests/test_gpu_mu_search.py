@@ -15,8 +15,9 @@ def dev(x):
     return torch.from_numpy(np.ascontiguousarray(x)).to("cuda")
 
 
-# values of mu per launch: 15 up to 273 matrices (frequencies times k-points), 4 at 1000, 1 above 4096 and for nao > 32
-@pytest.mark.parametrize("nao,nk,ntau", [(5, 3, 20), (4, 25, 40), (3, 60, 70), (33, 2, 12), (60, 1, 12)])
+# values of mu per launch, of a tree and of a way ahead: 15 / 15, 7 / 15, 3 / 15, 1 / 15 and 1 / 1
+@pytest.mark.parametrize("nao,nk,ntau", [(5, 3, 20), (8, 25, 40), (12, 30, 40), (20, 30, 40), (26, 30, 40), (33, 2, 12),
+                                         (60, 1, 12)])
 @pytest.mark.parametrize("gap", [False, True])
 def test_forms(nao, nk, ntau, gap):
     from paper_2206_07660_amd import gw
@@ -50,8 +51,8 @@ def test_forms(nao, nk, ntau, gap):
         ctx.close()
 
 
-# 48, 960 and 4320 matrices: 15, 4 and 1 values of mu per launch
-@pytest.mark.parametrize("mesh", [(2, 1, 1), (40, 1, 1), (12, 15, 1)])
+# 48, 960, 4320 and 17280 matrices of order 8: 15 / 15, 7 / 15, 3 / 15 and 1 / 1 values of mu per launch
+@pytest.mark.parametrize("mesh", [(2, 1, 1), (40, 1, 1), (12, 15, 1), (24, 30, 1)])
 @pytest.mark.parametrize("seed,mu0", [(8, 0.0), (32, 0.1), (39, 0.0)])
 def test_count_that_falls(mesh, seed, mu0):
     """24 nodes at beta 1000: in the gap the count of the sparse grids is not
