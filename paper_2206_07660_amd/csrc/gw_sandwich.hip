@@ -475,7 +475,12 @@ hipError_t vdot_launch(const void* V, int tv, const double2* X, double2* out, in
   return hipGetLastError();
 }
 
-// K-steps of 4 that hold nao, among the compiled counts
+// K-steps of 4 that hold nao, among the compiled counts: exact for nao 5 .. 8,
+// 13 .. 16, 21 .. 32 and some larger ones.  Counts between are left out to keep
+// the instantiations few (eight for each of five kernels): nao 9 .. 12 run 4
+// steps for 3 and 17 .. 20 run 6 for 5, where the polarization of one q (2x2x2,
+// nao 12 / 18, 24 nodes) still takes 49 / 142 us against 199 / 444 of the GEMMs
+// before.
 #define SAND_KS(nao, CALL)             \
   do {                                 \
     const int ks_ = ((nao) + 3) / 4;   \
