@@ -86,7 +86,8 @@ class SigmaFunction(torch.autograd.Function):
     When derivs.path runs the polarization in Hermitian mode (GWPath's
     default), G must be Hermitian per (tau, k); the forward checks this and
     raises ValueError otherwise (build the path with hermitian=False to
-    differentiate at a general complex G).  The VJP itself holds for any G."""
+    differentiate at a general complex G).  The VJP itself holds for any G where
+    P~ is kept from the forward; with per_q it is rebuilt in the path's mode."""
 
     @staticmethod
     def forward(ctx, G, derivs):
